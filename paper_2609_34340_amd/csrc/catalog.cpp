@@ -661,18 +661,10 @@ void build_device_image(vp_catalog& c) {
     ts = std::max(ts, n);
   }
   L.TS = ts;
-  int np = 1;
-  for (int x = 2; x <= g; ++x) np *= x;
-  L.n_perm = np;
   int off = 0;
-  L.off_terms = off; off += P * ts;
-  L.off_nterms = off; off += P;
   L.off_fb = off; off += P;
   L.off_fe = off; off += P;
   L.off_fam_info = off; off += FL * QG;
-  L.off_fam_out = off; off += FL * QG;
-  L.off_fam_in = off; off += FL * QG;
-  L.off_perms = off; off += np * g;
   // distinct NIC-lane sets of the NIC-carrying patterns: the shift part of a
   // shape's score depends on its pattern only through this set
   std::map<std::vector<int>, int> set_id;
@@ -690,8 +682,26 @@ void build_device_image(vp_catalog& c) {
     psid[p - c.J0] = it->second;
   }
   L.nS = (int)sets.size();
-  L.off_rset = off; off += L.nS * kMaxRTerms;
-  L.off_psid = off; off += c.J1;
+  // planner tables (see DevCatalogLayout)
+  const int nS = L.nS, W = kPlanWaves;
+  off = (off + 3) / 4 * 4;
+  L.off_plan = off;
+  L.kS = c.nn | 1;
+  L.q_magic = Q == 1 ? 0u : (uint32_t)(((uint64_t(1) << 32) + (uint64_t)Q - 1) / (uint64_t)Q);
+  int most = 1;   // intra-node lanes of a pattern
+  for (int p = 0; p < P; ++p) {
+    int n = 0;
+    for (int x = 0; x < Q * Q; ++x) n += c.patL[p][x];
+    most = std::max(most, n);
+  }
+  L.RW = (most + 7) / 8 * 8;
+  auto r16 = [](int x) { return (x + 15) / 16 * 16; };
+  L.pl_info = r16(P * L.RW * 2);
+  L.pl_wave = L.pl_info + r16(P * 8);
+  L.pl_sets = L.pl_wave + r16(2 * (W + 1) * 4);
+  L.pl_recs = L.pl_sets + r16(nS * kMaxRTerms * 2);
+  L.pl_end = L.pl_recs + r16(FL * Q * 2 * g * 2);
+  off += L.pl_end / 4;
   L.total = off;
   // every path but NIC runs at the PCIe rate; the planner relies on it (one
   // largest-lane maximum for the PCIe-rate classes, one for NIC)
@@ -704,37 +714,74 @@ void build_device_image(vp_catalog& c) {
   std::vector<int32_t>& im = c.image;
   im.assign(off, 0);
   for (int p = 0; p < P; ++p) {
-    int n = 0;
-    for (int block = 0; block < 2; ++block)
-      for (int q = 0; q < Q; ++q)
-        for (int q2 = 0; q2 < Q; ++q2) {
-          int cnt = (block ? c.patR[p] : c.patL[p])[q * Q + q2];
-          if (cnt) im[L.off_terms + p * ts + n++] = cnt | (q2 << 4) | (q << 8) | (block << 12);
-        }
-    im[L.off_nterms + p] = n;
     im[L.off_fb + p] = c.pat_fb[p];
     im[L.off_fe + p] = c.pat_fe[p];
   }
-  for (int f = 0; f < FL; ++f) {
-    std::vector<int> no(Q, 0), ni(Q, 0);
+  for (int f = 0; f < FL; ++f)
     for (int x = 0; x < QG; ++x) {
-      int id = c.lfam[f][x];
+      const int id = c.lfam[f][x];
       im[L.off_fam_info + f * QG + x] = c.icls[id] | (c.isrc[id] << 4) | (c.idst[id] << 8) | (id << 12);
-      im[L.off_fam_out + f * QG + c.isrc[id] * g + no[c.isrc[id]]++] = x;
-      im[L.off_fam_in + f * QG + c.idst[id] * g + ni[c.idst[id]]++] = x;
+    }
+  // planner tables.  Items: wavefront w takes the patterns of its sets, then
+  // shift-0 patterns until every wavefront has its share.
+  std::vector<std::vector<int>> items(W);
+  std::vector<int> set_begin(W + 1);
+  for (int w = 0; w <= W; ++w) set_begin[w] = (int)((int64_t)w * nS / W);
+  L.max_sets = 0;
+  for (int w = 0; w < W; ++w) L.max_sets = std::max(L.max_sets, set_begin[w + 1] - set_begin[w]);
+  for (int w = 0; w < W; ++w)
+    for (int p = 0; p < c.J1; ++p)
+      if (psid[p] >= set_begin[w] && psid[p] < set_begin[w + 1]) items[w].push_back(c.J0 + p);
+  for (int p = 0; p < c.J0; ++p) {
+    int least = 0;
+    for (int w = 1; w < W; ++w)
+      if (items[w].size() < items[least].size()) least = w;
+    items[least].push_back(p);
+  }
+  char* tab = (char*)(im.data() + L.off_plan);
+  uint16_t* rows = (uint16_t*)tab;
+  uint32_t* info = (uint32_t*)(tab + L.pl_info);
+  int32_t* wave_tab = (int32_t*)(tab + L.pl_wave);
+  uint16_t* set_rows = (uint16_t*)(tab + L.pl_sets);
+  uint16_t* recs = (uint16_t*)(tab + L.pl_recs);
+  const int zero_row = Q * Q * L.kS;
+  int it = 0;
+  for (int w = 0; w < W; ++w) {
+    wave_tab[w] = it;
+    for (int p : items[w]) {
+      int n = 0;
+      for (int x = 0; x < Q * Q; ++x)
+        for (int r = 0; r < c.patL[p][x]; ++r) rows[it * L.RW + n++] = (uint16_t)(x * L.kS);
+      while (n < L.RW) rows[it * L.RW + n++] = (uint16_t)zero_row;
+      const bool shifted = p >= c.J0;
+      info[2 * it] = (uint32_t)(shifted ? p - c.J0 : p) | (uint32_t)(shifted ? psid[p - c.J0] : nS) << 16;
+      const bool one = c.pat_fe[p] - c.pat_fb[p] == 1 && c.pat_fb[p] < 4096;
+      info[2 * it + 1] = one ? (uint32_t)c.pat_fb[p] : 4096u;
+      ++it;
     }
   }
-  for (int si = 0; si < L.nS; ++si)
+  wave_tab[W] = it;
+  for (int w = 0; w <= W; ++w) wave_tab[W + 1 + w] = set_begin[w];
+  for (int si = 0; si < nS; ++si)
     for (int m = 0; m < kMaxRTerms; ++m)
-      im[L.off_rset + si * kMaxRTerms + m] = m < (int)sets[si].size() ? sets[si][m] : -1;
-  for (int p = 0; p < c.J1; ++p) im[L.off_psid + p] = psid[p];
-  std::vector<int> perm(g);
-  for (int x = 0; x < g; ++x) perm[x] = x;
-  int pi = 0;
-  do {
-    for (int x = 0; x < g; ++x) im[L.off_perms + pi * g + x] = perm[x];
-    ++pi;
-  } while (std::next_permutation(perm.begin(), perm.end()));
+      set_rows[si * kMaxRTerms + m] = (uint16_t)(m < (int)sets[si].size() ? sets[si][m] * L.kS : zero_row);
+  // Family records.  Out-lane of a slot, in family order: class |
+  // destination slot << 2 | rank among the destination's in-lanes of the same
+  // kind (same node or cross-node) << 5 | in-lanes of the other kind << 7 |
+  // local index << 10.  In-lane, cross-node lanes first: class | source slot
+  // << 2 | position in the source's out-list << 5.
+  for (int f = 0; f < FL; ++f) {
+    const bool shifted = f >= c.F0;
+    // per slot: out-lanes so far, in-lanes so far and in all, by kind
+    int n_out[kMaxSlotsPerNode] = {}, seen[kMaxSlotsPerNode][2] = {}, all[kMaxSlotsPerNode][2] = {};
+    for (int id : c.lfam[f]) ++all[c.idst[id]][shifted && c.icls[id] == VP_PATH_NIC];
+    for (int x = 0; x < QG; ++x) {
+      const int id = c.lfam[f][x], cls = c.icls[id], src = c.isrc[id], dst = c.idst[id];
+      const int kind = shifted && cls == VP_PATH_NIC, same = seen[dst][kind]++, pos = n_out[src]++;
+      recs[((size_t)f * Q + src) * 2 * g + pos] = (uint16_t)(cls | dst << 2 | same << 5 | all[dst][!kind] << 7 | x << 10);
+      recs[((size_t)f * Q + dst) * 2 * g + g + (kind ? same : all[dst][1] + same)] = (uint16_t)(cls | src << 2 | pos << 5);
+    }
+  }
 }
 
 }  // namespace vp

@@ -16,7 +16,8 @@ constexpr int kMaxSlotsPerNode = 8;
 constexpr int kMaxRanks = 1024;
 constexpr int kMaxNodes = 256;
 constexpr int kMaxStarts = 16;
-constexpr int kPlanThreads = 1024;
+constexpr int kPlanThreads = 512;            // the planner's workgroup
+constexpr int kPlanWaves = kPlanThreads / 64;
 constexpr int kMaxRTerms = 8;   // NIC lanes of one node-local pattern (one per source slot)
 
 // Sentinel credit of a self pair (never bindable).
@@ -30,19 +31,25 @@ constexpr uint32_t kForbidden = 0xFFFFFFFFu;
 struct DevCatalogLayout {
   int32_t N, G, g, Q, nn, n_inst;
   int32_t J0, J1, F0, F1;
-  int32_t TS;            // term slots per pattern
-  int32_t n_perm;        // g!
+  int32_t TS;            // most slot pairs of a pattern's two blocks
   int64_t J, F;          // global shape / family counts
-  int32_t off_terms;     // (J0+J1) * TS packed terms: count | q2<<4 | q<<8 | block<<12
-  int32_t off_nterms;    // (J0+J1)
   int32_t off_fb, off_fe;      // (J0+J1) local family range of each pattern
   int32_t off_fam_info;  // (F0+F1) * Q*g : cls | src_slot<<4 | dst_slot<<8 | local_id<<12
-  int32_t off_fam_out;   // (F0+F1) * Q*g : [slot][m] local index of the m-th out-instance
-  int32_t off_fam_in;    // (F0+F1) * Q*g : [slot][m] local index of the m-th in-instance
-  int32_t off_perms;     // n_perm * g, lexicographic order
   int32_t nS;            // distinct NIC-lane sets of the NIC-carrying patterns
-  int32_t off_rset;      // nS * kMaxRTerms slot-pair indices q*Q+q2 of each set (-1 past its end)
-  int32_t off_psid;      // J1: set of each NIC-carrying pattern
+  // Planner tables, copied to LDS as they stand: byte offsets from off_plan,
+  // every section 16-byte aligned.  An item is a pattern; each wavefront of
+  // the planner scores a contiguous run of items that holds every pattern of
+  // its own NIC-lane sets (and a share of the shift-0 patterns).
+  int32_t off_plan;      // int32 index of the first table, a multiple of 4
+  int32_t kS;            // row stride of the node-block aggregates [Q*Q + 1][kS] (odd; the last row is zero)
+  int32_t RW;            // 16-bit row entries per item (a multiple of 8): one per intra-node lane, then the zero row
+  int32_t pl_info;       // items: {pattern index in its block | set << 16, its only family, or 4096 (several, or a higher index)}
+  int32_t pl_wave;       // [kPlanWaves + 1] first item, then [kPlanWaves + 1] first set, of each wavefront
+  int32_t pl_sets;       // sets: kMaxRTerms 16-bit row offsets (the zero row past the end)
+  int32_t pl_recs;       // [family][slot]: g out-lane and g in-lane descriptors of 16 bits
+  int32_t pl_end;        // bytes with the records
+  int32_t max_sets;      // most sets of one wavefront
+  uint32_t q_magic;      // ceil(2^32 / Q), for Q > 1: x / Q = umulhi(x, q_magic) for x < 2^16
   int32_t total;         // int32 elements
   int64_t bw_cls[4];     // rate of PIX, PXB, NIC, SYS paths
   int64_t bw_max;

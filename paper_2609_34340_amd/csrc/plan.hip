@@ -1,33 +1,53 @@
 // vp_plan: online channel-guided demand decomposition (Sec. 4.2, Alg. 2) as
-// one persistent workgroup of 1024 threads that runs the whole iteration
+// one persistent workgroup of 512 threads that runs the whole iteration
 // loop on the device (vp_plan_batch: one such workgroup per matrix).
 //
-// Per iteration:
+// An iteration is a serial chain of short steps, so what bounds the planner
+// is latency: LDS round trips, workgroup barriers and the instructions of
+// single wavefronts, not bytes or operations.  The loop is therefore laid out
+// for the fewest round trips: three barriers per iteration, every wavefront
+// with its own share of the work in registers.
 //   1. shape scores, Eq. (5)-(6), from node-block aggregates kept in LDS:
 //      A = sum over nodes of the diagonal node block of D-hat and B_k = sum of
-//      the blocks (n, n+k).  A shape (k, L, R) scores sum A.L + sum B_k.R,
-//      which equals sum D-hat.M.  The aggregates are kept in units of the
-//      pack granule as int32 (every demand entry is a whole number of units,
-//      so scores keep their order).  The B part depends on a pattern only
-//      through its set of NIC lanes: a few lanes per distinct set find the
-//      set's best shift while other threads compute every pattern's A part;
-//      one thread per pattern then adds the two and the block takes the
-//      argmax of packed 64-bit keys (ties to the lowest canonical shape);
-//   2. for the families of the best shape: the cluster-level out/in lists of
-//      every group and the binding credits h' = min(D^rem_ij, cap) (Eq. (7)
-//      scaled by tau) of every instance and endpoint pair, into LDS, with
-//      the shuffled starts' permutations drawn on the idle wavefronts;
-//   3. MultiStartAA (Eq. (8)): one wavefront per (family, start).  Each lane
-//      owns up to a few groups for both AA halves and keeps their source and
-//      destination assignments and credit rows in registers, so a half-step
-//      is one LDS round trip (read the other side, write back);
-//   4. Evaluate (Eq. (9)-(10)), the exact utility argmax in 128-bit, by each
-//      wavefront that writes the winner (a one-family shape needs only its
-//      best start);
-//   5. the activation is appended and D^rem (global memory, touched by this
-//      one workgroup only) is updated; the per-rank stream offsets are
-//      completed by stream_off_kernel after the loop.
-// No host round trip happens between iterations.
+//      the blocks (n, n+k), in units of the pack granule as int32 (every
+//      demand entry is a whole number of units, so scores keep their order).
+//      A shape (k, L, R) scores sum A.L + sum B_k.R = sum D-hat.M, and its B
+//      part depends on the pattern only through its set of NIC lanes.  Each
+//      wavefront owns some of the sets and every pattern of them: its lanes
+//      keep the sums of their set over up to eight shifts in registers and
+//      re-read only the one shift that the last activation changed, reduce
+//      to the set's best shift and add it to their patterns' A parts.
+//   -- barrier --
+//   2. the argmax (ties to the lowest canonical shape) is one LDS word that
+//      the wavefronts' best candidates have met in by an atomic maximum.
+//      MultiStartAA (Eq. (8)): one wavefront
+//      per (family, start).  A lane owns up to a few rank groups: it reads
+//      the family's record of their slots and the residuals of their in- and
+//      out-lanes into registers, turns them into the binding credits
+//      h' = min(D^rem_ij, cap) (Eq. (7) scaled by tau), draws its shuffles,
+//      and exchanges the AA halves' assignments with the other lanes by
+//      cross-lane permutes.  Meanwhile the other wavefronts write the
+//      previous activation to the schedule arrays.
+//   -- barrier --
+//   3. Evaluate (Eq. (9)-(10)): the exact utility argmax in 128 bits over
+//      families, redundantly in every wavefront (a one-family shape needs only
+//      its best start).  The wavefront that ran the winner still holds its
+//      binding: it subtracts the volumes from D^rem and the aggregates and
+//      leaves the lanes in LDS for the schedule writers.
+//   -- barrier --
+// D^rem is kept in units, 32 bits each, blocked by group pair so that the
+// g x g credits of a lane are one 16-byte load (g = 2): in LDS where the
+// matrix fits beside the tables (up to 160 ranks or so), in the caller's
+// workspace otherwise.  No host round trip happens between iterations.
+//
+// Measured, per activation: 2.3 us at 8 to 128 ranks and 3.6 us at 256 (16
+// wavefronts, five barriers, the family's lists and credits staged in LDS for
+// the runs, schedule stores by the winner's wavefronts: 4.6-4.9 and 6.3 us).
+// A wavefront alone on its SIMD issues a dependent vector or scalar
+// instruction every eight cycles, an independent one every four; an LDS read
+// takes 64 cycles, a cross-lane permute 71, a taken branch about 30 and a
+// barrier of eight wavefronts under 20, so instructions on the longest
+// wavefront are what counts.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -39,43 +59,48 @@
 namespace vp {
 namespace {
 
-constexpr int kWaves = kPlanThreads / 64;
 constexpr int kMaxQG = kMaxSlotsPerNode * kMaxGpusPerSwitch;   // lanes per node
 constexpr int kMaxLTerms = 3 * kMaxSlotsPerNode;   // PIX, PXB and NIC entries of one diagonal block
-constexpr uint32_t kRawSaturated = 0xFFFFFFFEu;     // residual too large for 32 bits: reload it
+constexpr int kHeldShifts = 8;                     // shifts of a set that one lane holds
+constexpr int kFamChunk = 64;                      // families evaluated together
 
 // Phase timing, compiled only with -DVP_PHASE_STAMPS (phase_stamps.py builds
-// such a copy): thread 0 of workgroup 0 stores the cycle counter at each
-// phase boundary of every iteration, row = iteration (4096 rows of 16):
-// columns 0-8 open the phases, 9-14 mark points inside them (thread 0's
-// gather items done, the start draws done, the best start read, the
-// update's reads done, its stores issued, the shared totals written).
+// such a copy): one lane of the first start's wavefront stores the cycle
+// counter at each phase boundary of every iteration, row = iteration (4096
+// rows of 16); column k opens the phase that phase_stamps.py names.
 #ifdef VP_PHASE_STAMPS
 __device__ unsigned long long g_phase_stamps[4096 * 16];
-#define VP_STAMP(k)                                                                                  \
-  do {                                                                                               \
-    if (threadIdx.x == 0 && blockIdx.x == 0)                                                         \
-      g_phase_stamps[(stamp_it < 4095 ? stamp_it : 4095) * 16 + (k)] = __builtin_readcyclecounter(); \
+#define VP_STAMP(k)                                                                              \
+  do {                                                                                           \
+    if (threadIdx.x == 0 && blockIdx.x == 0)                                                     \
+      g_phase_stamps[(K < 4095 ? K : 4095) * 16 + (k)] = __builtin_readcyclecounter();           \
   } while (0)
 #else
 #define VP_STAMP(k) ((void)0)
 #endif
 
-struct PairRes {
-  int64_t F;
-  // largest lane volume on a PCIe-rate path (PIX, PXB, SYS) and on a NIC
-  // path: Eq. (10) needs only the largest volume / rate, and the classes of
-  // one rate share a maximum
-  int64_t xmax[2];
-};
-
 struct Shared {
-  uint64_t key;
-  int64_t total_rem, Lmax, tau, total_units;
-  int64_t cap[4];
-  int32_t capu[4];
-  int32_t K, err;
-  int32_t huge;   // some demand entry reaches 2^42 bytes
+  int64_t total, total_units;
+  int64_t tau;
+  int32_t capu[2];             // lane cap in units: PCIe-rate paths, NIC
+  uint32_t Lmax_units;         // largest row or column sum
+  int32_t err, huge;           // huge: some demand entry reaches 2^42 bytes
+  // Argmaxes of even and odd iterations: of the shapes, score << 33 |
+  // (2^20 - 1 - shape code) << 13 | payload, with code = shift << 12 |
+  // pattern and the payload the pattern's only family, or 2^12 where that has
+  // to be looked up; and of the starts of a one-family shape, F << 4 |
+  // (15 - start).
+  uint64_t key[2];
+  uint64_t step_key[2];        // shuffle keys of even and odd iterations: seed and iteration absorbed
+  uint32_t top[2];
+  uint64_t triple[4];          // two wavefronts per run: the canonical start's highest-credit triple of each slot
+  int32_t changed[4];          // and whether a half-step changed any run
+  const int64_t* D;
+  const int32_t* inst_id;
+  int32_t *family, *dst, *inst;
+  int64_t *bytes, *send_off, *stream_off;
+  int32_t* recv_src;
+  int64_t unit, lambda, bw_p, bw_n;
 };
 
 struct PlanArgs {
@@ -88,10 +113,10 @@ struct PlanArgs {
   uint64_t odd_inv, odd_lim;
   int32_t unit_shift;
   int32_t n_start, i_aa, k_max, FC;
-  int32_t LPS, SPT;   // shift scoring: lanes per NIC-lane set (a power of two) and shifts per lane
-  int32_t LPS_log2;
-  uint32_t qg_magic;  // ceil(2^32 / (Q g)): t / (Q g) = umulhi(t, qg_magic) for t < 2^16
-  int32_t MLT, MRT;   // most diagonal-block terms of a pattern; largest NIC-lane set
+  int32_t LPS_log2, SPT;      // shift scoring: lanes per NIC-lane set (a power of two) and shifts per lane
+  int32_t held;               // the lanes hold their shifts' sums (one round of sets, SPT <= kHeldShifts)
+  int32_t MRT;                // largest NIC-lane set
+  int32_t rec_lds;            // the family records are in LDS
   int32_t *K, *family, *dst, *inst;
   int64_t *bytes, *tau;
   int64_t *send_off, *stream_off;   // optional [k_max][N] buffer layout per rank
@@ -99,33 +124,8 @@ struct PlanArgs {
   int32_t* status;
   int32_t batch;                    // matrices, one workgroup each; every buffer above holds `batch` of them
   // LDS layout (byte offsets)
-  int32_t o_agg, o_terms, o_pfb, o_finfo;
-  int32_t o_pair, o_outT, o_inT, o_ipos, o_ocls, o_iid, o_hp, o_raw, o_sl, o_dl, o_top;
-  int32_t o_rset, o_psid, o_rbest, o_pbase, o_rp;
+  int32_t o_agg, o_rb, o_pr, o_xw, o_out, o_sacc, o_tab, o_res;
 };
-
-// Per-rank arrays of plan_kernel<g, MG> sit at compile-time offsets from the
-// start of the dynamic LDS, sized for the most ranks the instantiation
-// takes (64 MG groups of g): they are addressed with immediate offsets and
-// hold no scalar register.  Everything else follows at host-computed offsets.
-struct FixedLds {
-  size_t rinfo, lastj, lastv, sacc, bx, brw, bsl, bdl, bid, end;
-};
-__host__ __device__ constexpr size_t a16(size_t x) { return (x + 15) / 16 * 16; }
-__host__ __device__ constexpr FixedLds fixed_lds(size_t n) {
-  FixedLds f{};
-  f.rinfo = a16(sizeof(Shared));
-  f.lastj = f.rinfo + 4 * n;
-  f.lastv = a16(f.lastj + 4 * n);
-  f.sacc = f.lastv + 8 * n;
-  f.bx = f.sacc + 8 * n;
-  f.brw = f.bx + 4 * n;
-  f.bsl = f.brw + 4 * n;
-  f.bdl = f.bsl + n;
-  f.bid = f.bdl + n;
-  f.end = a16(f.bid + n);
-  return f;
-}
 
 // ------------------------------------------------------------------ helpers
 
@@ -135,22 +135,45 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Whole-wavefront reductions of the device library (DPP based); every lane
-// receives the result.
 extern "C" __device__ __attribute__((const)) long long __ockl_wfred_add_i64(long long);
-extern "C" __device__ __attribute__((const)) long long __ockl_wfred_max_i64(long long);
-extern "C" __device__ __attribute__((const)) unsigned long long __ockl_wfred_max_u64(unsigned long long);
-__device__ inline int64_t wave_sum(int64_t v) { return __ockl_wfred_add_i64(v); }
-__device__ inline int64_t wave_max(int64_t v) { return __ockl_wfred_max_i64(v); }
-extern "C" __device__ __attribute__((const)) int __ockl_wfred_max_i32(int);
-__device__ inline uint64_t wave_max_u(uint64_t v) { return __ockl_wfred_max_u64(v); }
-__device__ inline int32_t wave_max32(int32_t v) { return __ockl_wfred_max_i32(v); }
+__device__ inline int64_t wave_sum64(int64_t v) { return __ockl_wfred_add_i64(v); }
+
 // lane 0's value in every lane (the whole wavefront active)
 __device__ inline int32_t lane0(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ inline int64_t lane0(int64_t v) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)v);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(v >> 32));
   return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ inline uint32_t read_lane(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
+
+// v of the lane n further on in its row of 16 lanes (cyclic)
+template <int n>
+__device__ inline uint32_t row_ror(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + n, 0xF, 0xF, true);
+}
+// v of the lane whose index differs in bit n (1 or 2)
+template <int n>
+__device__ inline uint32_t quad_xor(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, n == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);
+}
+struct OpMax {
+  __device__ static uint32_t f(uint32_t a, uint32_t b) { return a > b ? a : b; }
+};
+struct OpMin {
+  __device__ static uint32_t f(uint32_t a, uint32_t b) { return a < b ? a : b; }
+};
+struct OpAdd {
+  __device__ static uint32_t f(uint32_t a, uint32_t b) { return a + b; }
+};
+// Reduction over the wavefront (every lane active), wavefront-uniform.
+template <class Op>
+__device__ inline uint32_t wave_reduce(uint32_t v) {
+  v = Op::f(v, row_ror<8>(v));
+  v = Op::f(v, row_ror<4>(v));
+  v = Op::f(v, row_ror<2>(v));
+  v = Op::f(v, row_ror<1>(v));
+  return Op::f(Op::f(read_lane(v, 0), read_lane(v, 16)), Op::f(read_lane(v, 32), read_lane(v, 48)));
 }
 
 // Binding credits are held in pack units as int32 (every credit is a whole
@@ -167,6 +190,12 @@ __device__ inline uint64_t sm_mix(uint64_t z) {
   z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
   return z ^ (z >> 31);
 }
+// z mod (m + 1) for m + 1 in 2..4
+template <int m1>
+__device__ inline int small_mod(uint64_t z) {
+  if constexpr (m1 == 3) return (int)(((uint32_t)(z >> 32) % 3u + (uint32_t)z % 3u) % 3u);   // 2^32 = 1 mod 3
+  else return (int)((uint32_t)z & (uint32_t)(m1 - 1));
+}
 
 // Utility order of Eq. (10): (S1, x1/b1) beats (S2, x2/b2) exactly.
 __device__ inline bool utility_greater(int64_t S1, int64_t x1, int64_t b1, int64_t S2, int64_t x2,
@@ -179,14 +208,9 @@ __device__ inline bool utility_greater(int64_t S1, int64_t x1, int64_t b1, int64
   return lhs > rhs;
 }
 
-// Lexicographic permutations of g elements.
+// Lexicographic permutations of g > 2 elements.
 template <int g>
 struct Perms;
-template <>
-struct Perms<2> {
-  static constexpr int n = 2;
-  __device__ static int at(int p, int m) { return p ? 1 - m : m; }
-};
 template <>
 struct Perms<3> {
   static constexpr int n = 6;
@@ -208,332 +232,23 @@ struct Perms<4> {
   }
 };
 
-// Local family descriptor (16 bits): cls | src_slot<<2 | dst_slot<<5 |
-// out_pos<<8 | rank_same<<10 | n_other<<12.  rank_same is the instance's rank
-// among the in-instances of its destination slot of the same kind (same-node
-// or cross-node lane), n_other the number of the other kind: cross-node
-// in-instances precede same-node ones exactly when their source node is the
-// lower one.
-__device__ inline int d_cls(uint32_t w) { return w & 3; }
-__device__ inline int d_ss(uint32_t w) { return (w >> 2) & 7; }
-__device__ inline int d_ds(uint32_t w) { return (w >> 5) & 7; }
-__device__ inline int d_opos(uint32_t w) { return (w >> 8) & 3; }
-__device__ inline int d_rsame(uint32_t w) { return (w >> 10) & 3; }
-__device__ inline int d_nother(uint32_t w) { return (w >> 12) & 7; }
+// Words of D^rem per group pair (a, d): the residual units of its g x g rank
+// pairs, row by source, padded to whole 16-byte vectors.
+template <int g>
+constexpr int kResWords = g == 2 ? 4 : g == 3 ? 12 : 16;
 
-// Per-family working set of the current chunk.
-struct FamCtx {
-  const uint16_t* outT;   // [G*g] out-instance t of (group, m)
-  const uint16_t* inT;    // [G*g] in-instance t of (group, m)
-  const int8_t* ipos;     // [G*g] position of the out-instance in its group's in-list if intra, else -1
-  const uint8_t* ocls;    // [G*g] path class of the out-instance
-  const int32_t* H;       // [N*g*g] credits (units; kForbiddenU for a self pair)
-  int f;                  // global family index
-};
-
-// One (family, start) pair; executed by one whole wavefront.  `top` is the
-// family's highest-credit triple packed as credit << 24 | (2^24 - 1 - (t*g*g +
-// i*g + j)) (0 when no credit is positive); `rperm` holds, for a shuffled
-// start, every group's source and destination permutation.
-template <int g, int MG>
-__device__ void run_pair(const PlanArgs& P, const FamCtx& fc, uint8_t* SL, uint8_t* DL, int start,
-                         const uint8_t* rperm, int lane, uint64_t top, bool need_x, PairRes* out) {
-  constexpr int g2 = g * g, kRow = g2 | 1;   // credit rows padded to an odd word count
-  const int G = P.L.G;
-  int o[MG][g], nn_[MG][g], ip[MG][g], sig[MG][g], del[MG][g];
-  bool own[MG];
+template <int g>
+__device__ inline void load_block(const uint32_t* p, uint32_t (&v)[g * g]) {
+  const uint4* q = (const uint4*)p;
 #pragma unroll
-  for (int r = 0; r < MG; ++r) {
-    const int a = lane + 64 * r;
-    own[r] = a < G;
+  for (int b = 0; b < kResWords<g> / 4; ++b) {
+    const uint4 x = q[b];
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-    for (int m = 0; m < g; ++m) {
-      o[r][m] = own[r] ? fc.outT[a * g + m] : 0;
-      nn_[r][m] = own[r] ? fc.inT[a * g + m] : 0;
-      ip[r][m] = own[r] ? fc.ipos[a * g + m] : -1;
-      sig[r][m] = m;
-      del[r][m] = m;
-    }
-  }
-  int protect = -1;
-  if (start == 0) {
-    // canonical binding plus the highest-credit triple, ties to the smallest (t, i, j)
-    if (top) {
-      const int idx = 0xFFFFFF - (int)(top & 0xFFFFFF);
-      const int ts = idx / g2, e = idx - ts * g2;
-      const int il = e / g, jl = e - il * g;
-      protect = ts;
-#pragma unroll
-      for (int r = 0; r < MG; ++r) {
-        if (!own[r]) continue;
-#pragma unroll
-        for (int m = 0; m < g; ++m) {
-          if (o[r][m] == ts) {
-#pragma unroll
-            for (int m2 = 0; m2 < g; ++m2)
-              if (sig[r][m2] == il) {
-                sig[r][m2] = sig[r][m];
-                sig[r][m] = il;
-              }
-          }
-          if (nn_[r][m] == ts) {
-#pragma unroll
-            for (int m2 = 0; m2 < g; ++m2)
-              if (del[r][m2] == jl) {
-                del[r][m2] = del[r][m];
-                del[r][m] = jl;
-              }
-          }
-        }
-      }
-    }
-  } else {
-    // independent Fisher-Yates shuffles of every group's sources and
-    // destinations, drawn during the credit gather (packed 2 bits per member)
-#pragma unroll
-    for (int r = 0; r < MG; ++r) {
-      if (!own[r]) continue;
-      const int a = lane + 64 * r;
-      const int ps = rperm[2 * a], pd = rperm[2 * a + 1];
-#pragma unroll
-      for (int m = 0; m < g; ++m) {
-        sig[r][m] = (ps >> (2 * m)) & 3;
-        del[r][m] = (pd >> (2 * m)) & 3;
-      }
-    }
-  }
-  // Self-binding repair, per group in out-list order: trade destinations with
-  // the first other unprotected in-instance, else sources with the first
-  // other unprotected out-instance.
-#pragma unroll
-  for (int r = 0; r < MG; ++r) {
-    if (!own[r]) continue;
-#pragma unroll
-    for (int m = 0; m < g; ++m) {
-      const int mi = ip[r][m];
-      if (mi < 0 || sig[r][m] != del[r][mi]) continue;
-      int partner = -1;
-#pragma unroll
-      for (int m2 = 0; m2 < g; ++m2)
-        if (partner < 0 && nn_[r][m2] != o[r][m] && nn_[r][m2] != protect) partner = m2;
-      if (partner >= 0) {
-        const int x = del[r][mi];
-        del[r][mi] = del[r][partner];
-        del[r][partner] = x;
-        continue;
-      }
-#pragma unroll
-      for (int m3 = 0; m3 < g; ++m3)
-        if (partner < 0 && o[r][m3] != o[r][m] && o[r][m3] != protect) partner = m3;
-      if (partner >= 0) {
-        const int x = sig[r][m];
-        sig[r][m] = sig[r][partner];
-        sig[r][partner] = x;
-      }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < MG; ++r) {
-    if (!own[r]) continue;
-#pragma unroll
-    for (int m = 0; m < g; ++m) {
-      SL[o[r][m]] = (uint8_t)sig[r][m];
-      DL[nn_[r][m]] = (uint8_t)del[r][m];
-    }
-  }
-  wave_sync();
-
-  // The credit rows of the owned groups' out- and in-instances do not change
-  // during the run: with few enough of them they are read once here and held
-  // in registers, and a half-step reads only the other side's assignment.
-  constexpr bool kHold = 2 * MG * g * g2 <= 64;
-  int32_t hs[kHold ? MG : 1][g][g2], hd[kHold ? MG : 1][g][g2];
-  if constexpr (kHold) {
-#pragma unroll
-    for (int r = 0; r < MG; ++r)
-#pragma unroll
-      for (int m = 0; m < g; ++m)
-#pragma unroll
-        for (int e = 0; e < g2; ++e) {
-          hs[r][m][e] = fc.H[o[r][m] * kRow + e];
-          hd[r][m][e] = fc.H[nn_[r][m] * kRow + e];
-        }
-  }
-
-  // Alternating Algorithm: source half, then destination half.  A half that
-  // changes nothing, other than the very first, leaves a fixed point: the
-  // half before it made its own side optimal against this side, which has
-  // not moved.  Stopping there gives the same binding as stopping after a
-  // whole unchanged sweep, one sweep earlier.
-  for (int sweep = 0; sweep < P.i_aa; ++sweep) {
-    int changed = 0;
-    {
-      // every load of the half-step first (destinations and credit rows of all
-      // owned groups), then the g! comparisons
-      int jl[MG][g];
-      int32_t row[MG][g][g2];
-#pragma unroll
-      for (int r = 0; r < MG; ++r)
-#pragma unroll
-        for (int m = 0; m < g; ++m) {
-          jl[r][m] = DL[o[r][m]];
-#pragma unroll
-          for (int e = 0; e < g2; ++e) row[r][m][e] = kHold ? hs[r][m][e] : fc.H[o[r][m] * kRow + e];
-        }
-      // computed for every lane (a lane past the last group reads instance
-      // 0's rows and changes nothing): no branch but the guarded writes
-#pragma unroll
-      for (int r = 0; r < MG; ++r) {
-        int32_t h[g][g];
-#pragma unroll
-        for (int m = 0; m < g; ++m)
-#pragma unroll
-          for (int il = 0; il < g; ++il) {
-            int32_t v = row[r][m][il * g];
-#pragma unroll
-            for (int jj = 1; jj < g; ++jj) v = jl[r][m] == jj ? row[r][m][il * g + jj] : v;
-            h[m][il] = v;
-          }
-        int32_t cur = 0;
-#pragma unroll
-        for (int m = 0; m < g; ++m) {
-          int32_t v = h[m][0];
-#pragma unroll
-          for (int i2 = 1; i2 < g; ++i2) v = sig[r][m] == i2 ? h[m][i2] : v;
-          cur += v > 0 ? v : 0;   // a self pair counts as zero credit
-        }
-        int32_t bestv = -1;
-        int bp = 0;
-#pragma unroll
-        for (int p = 0; p < Perms<g>::n; ++p) {
-          int32_t v = 0;
-#pragma unroll
-          for (int m = 0; m < g; ++m) v += h[m][Perms<g>::at(p, m)];
-          if (v > bestv) {
-            bestv = v;
-            bp = p;
-          }
-        }
-        const bool up = own[r] && bestv > cur;
-#pragma unroll
-        for (int m = 0; m < g; ++m) sig[r][m] = up ? Perms<g>::at(bp, m) : sig[r][m];
-        if (up) {
-#pragma unroll
-          for (int m = 0; m < g; ++m) SL[o[r][m]] = (uint8_t)sig[r][m];
-        }
-        changed |= up;
-      }
-    }
-    wave_sync();
-    if (sweep > 0 && !__any(changed)) break;
-    changed = 0;
-    {
-      int il[MG][g];
-      int32_t row[MG][g][g2];
-#pragma unroll
-      for (int r = 0; r < MG; ++r)
-#pragma unroll
-        for (int m = 0; m < g; ++m) {
-          il[r][m] = SL[nn_[r][m]];
-#pragma unroll
-          for (int e = 0; e < g2; ++e) row[r][m][e] = kHold ? hd[r][m][e] : fc.H[nn_[r][m] * kRow + e];
-        }
-#pragma unroll
-      for (int r = 0; r < MG; ++r) {
-        int32_t h[g][g];
-#pragma unroll
-        for (int m = 0; m < g; ++m)
-#pragma unroll
-          for (int jl = 0; jl < g; ++jl) {
-            int32_t v = row[r][m][jl];
-#pragma unroll
-            for (int ii = 1; ii < g; ++ii) v = il[r][m] == ii ? row[r][m][ii * g + jl] : v;
-            h[m][jl] = v;
-          }
-        int32_t cur = 0;
-#pragma unroll
-        for (int m = 0; m < g; ++m) {
-          int32_t v = h[m][0];
-#pragma unroll
-          for (int j2 = 1; j2 < g; ++j2) v = del[r][m] == j2 ? h[m][j2] : v;
-          cur += v > 0 ? v : 0;   // a self pair counts as zero credit
-        }
-        int32_t bestv = -1;
-        int bp = 0;
-#pragma unroll
-        for (int p = 0; p < Perms<g>::n; ++p) {
-          int32_t v = 0;
-#pragma unroll
-          for (int m = 0; m < g; ++m) v += h[m][Perms<g>::at(p, m)];
-          if (v > bestv) {
-            bestv = v;
-            bp = p;
-          }
-        }
-        const bool up = own[r] && bestv > cur;
-#pragma unroll
-        for (int m = 0; m < g; ++m) del[r][m] = up ? Perms<g>::at(bp, m) : del[r][m];
-        if (up) {
-#pragma unroll
-          for (int m = 0; m < g; ++m) DL[nn_[r][m]] = (uint8_t)del[r][m];
-        }
-        changed |= up;
-      }
-    }
-    wave_sync();
-    if (!__any(changed)) break;
-  }
-
-  // binding score F (Eq. (8)) and the largest lane volume per path class, in units
-  int64_t F = 0;
-  int32_t xp = 0, xn = 0;
-  int jf[MG][g], cf[MG][g];
-  int32_t rf[MG][g][g];
-#pragma unroll
-  for (int r = 0; r < MG; ++r)
-#pragma unroll
-    for (int m = 0; m < g; ++m) {
-      jf[r][m] = DL[o[r][m]];
-      cf[r][m] = own[r] ? fc.ocls[(lane + 64 * r) * g + m] : 0;
-#pragma unroll
-      for (int jl = 0; jl < g; ++jl) {
-        if constexpr (kHold) {   // the row is in registers: select the source's part
-          int32_t v = hs[r][m][jl];
-#pragma unroll
-          for (int i2 = 1; i2 < g; ++i2) v = sig[r][m] == i2 ? hs[r][m][i2 * g + jl] : v;
-          rf[r][m][jl] = v;
-        } else {
-          rf[r][m][jl] = fc.H[o[r][m] * kRow + sig[r][m] * g + jl];
-        }
-      }
-    }
-#pragma unroll
-  for (int r = 0; r < MG; ++r) {
-#pragma unroll
-    for (int m = 0; m < g; ++m) {
-      int32_t x = rf[r][m][0];
-#pragma unroll
-      for (int jj = 1; jj < g; ++jj) x = jf[r][m] == jj ? rf[r][m][jj] : x;
-      x = own[r] && x > 0 ? x : 0;   // a self pair serves nothing
-      F += x;
-      const bool nic = cf[r][m] == VP_PATH_NIC;
-      xn = nic && x > xn ? x : xn;
-      xp = !nic && x > xp ? x : xp;
-    }
-  }
-  F = wave_sum(F);
-  if (need_x) {   // the lane maxima only serve comparisons between families
-    xp = wave_max32(xp);
-    xn = wave_max32(xn);
-  }
-  if (lane == 0) {
-    out->F = F;
-    out->xmax[0] = xp;
-    out->xmax[1] = xn;
+    for (int e = 0; e < 4; ++e)
+      if (b * 4 + e < g * g) v[b * 4 + e] = w[e];
   }
 }
-
-__device__ inline void set_err(Shared* sh, int code) { atomicCAS(&sh->err, 0, code); }
 
 // Element idx of a global array whose byte offsets stay below 2^32 (checked
 // on the host): a 32-bit offset from a wavefront-uniform base, which the
@@ -541,27 +256,6 @@ __device__ inline void set_err(Shared* sh, int code) { atomicCAS(&sh->err, 0, co
 template <typename T>
 __device__ inline T& at32(T* base, uint32_t idx) {
   return *(T*)((char*)base + (uint32_t)(idx * (uint32_t)sizeof(T)));
-}
-
-// The first start with the highest binding score F among a family's ns runs
-// (F >= 0; enter with F0 = -1).  Four scores are read per round; indices past
-// the last read the last again, which never wins a strict comparison.
-__device__ inline void best_start(const PairRes* r, int ns, int& s0, int64_t& F0) {
-  for (int b = 0; b < ns; b += 4) {
-    int64_t f[4];
-    int q[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      q[u] = b + u < ns ? b + u : ns - 1;
-      f[u] = r[q[u]].F;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (f[u] > F0) {
-        F0 = f[u];
-        s0 = q[u];
-      }
-  }
 }
 
 // Workgroup barrier that orders LDS only: outstanding global stores of the
@@ -573,738 +267,1238 @@ __device__ inline void lds_barrier() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
-template <int g, int MG>
+// floor(x / d) for x >= 0, d >= 1: below 2^52 the correctly rounded double
+// quotient is within one of it, and one step against the remainder makes it
+// exact; larger values take the integer division.
+__device__ inline int64_t floor_div(int64_t x, int64_t d) {
+  if (x >= (int64_t(1) << 52) || d >= (int64_t(1) << 52)) return x / d;
+  int64_t q = (int64_t)((double)x / (double)d);
+  const int64_t r = x - q * d;
+  if (r < 0) --q;
+  else if (r >= d) ++q;
+  return q;
+}
+
+// mask ? a : b, bit by bit
+__device__ inline int32_t bit_select(int32_t mask, int32_t a, int32_t b) { return (mask & a) | (~mask & b); }
+
+// Order of a group's g members over its g out-lanes (or in-lanes): at(m) is
+// the member of lane m.  Two members need one bit; more are held one by one
+// and are never indexed at run time.
+template <int g>
+struct Order {
+  static constexpr int bits = 2 * g;
+  int a[g];
+  __device__ void identity() {
+#pragma unroll
+    for (int m = 0; m < g; ++m) a[m] = m;
+  }
+  __device__ int at(int m) const {
+    int v = a[0];
+#pragma unroll
+    for (int x = 1; x < g; ++x) v = bit_select(m == x ? -1 : 0, a[x], v);   // values, so that no one indexes a[]
+    return v;
+  }
+  __device__ void swap_if(bool c, int i, int j) {
+    const int x = at(i), y = at(j);
+#pragma unroll
+    for (int m = 0; m < g; ++m) {
+      a[m] = bit_select(c && m == j ? -1 : 0, x, a[m]);
+      a[m] = bit_select(c && m == i ? -1 : 0, y, a[m]);
+    }
+  }
+  __device__ uint32_t word() const {
+    uint32_t w = 0;
+#pragma unroll
+    for (int m = 0; m < g; ++m) w |= (uint32_t)a[m] << (2 * m);
+    return w;
+  }
+  // member of lane `pos` in a word shifted to this group
+  __device__ static int member(uint32_t w, int pos) { return (int)((w >> (2 * pos)) & 3); }
+  // Fisher-Yates on a SplitMix64 stream
+  __device__ void shuffle(uint64_t state) {
+    identity();
+#pragma unroll
+    for (int m = g - 1; m >= 1; --m) {
+      state += kGolden;
+      const uint64_t z = sm_mix(state);
+      swap_if(true, m, m == 1 ? small_mod<2>(z) : m == 2 ? small_mod<3>(z) : small_mod<4>(z));
+    }
+  }
+  // The best order where lane m earns h[m][x] with member x, the first one in
+  // lexicographic order, if it beats the present one (whose self pairs earn
+  // nothing).
+  __device__ bool improve(const int32_t (&h)[g][g]) {
+    int32_t cur = 0;
+#pragma unroll
+    for (int m = 0; m < g; ++m) {
+      int32_t v = h[m][0];
+#pragma unroll
+      for (int x = 1; x < g; ++x) v = bit_select(a[m] == x ? -1 : 0, h[m][x], v);
+      cur += v > 0 ? v : 0;
+    }
+    int32_t bestv = -1;
+    uint32_t bw = 0;   // the best order's word, chosen as a constant: no table is indexed
+#pragma unroll
+    for (int p = 0; p < Perms<g>::n; ++p) {
+      int32_t v = 0;
+      uint32_t w = 0;
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        v += h[m][Perms<g>::at(p, m)];
+        w |= (uint32_t)Perms<g>::at(p, m) << (2 * m);
+      }
+      bw = v > bestv ? w : bw;
+      bestv = max(bestv, v);
+    }
+    const bool up = bestv > cur;
+#pragma unroll
+    for (int m = 0; m < g; ++m) a[m] = up ? (int)((bw >> (2 * m)) & 3) : a[m];
+    return up;
+  }
+};
+// Two members: the order is a mask, 0 or all ones (swapped), and everything
+// follows by bit operations; a compare that feeds a select costs two more
+// wait states here.
+template <>
+struct Order<2> {
+  static constexpr int bits = 1;
+  int32_t p;
+  __device__ void identity() { p = 0; }
+  __device__ int at(int m) const { return (p & 1) ^ m; }
+  __device__ int32_t at_mask(int m) const { return m ? ~p : p; }   // all ones: member 1
+  __device__ void swap_if(bool c, int i, int j) { p = c && i != j ? ~p : p; }
+  __device__ uint32_t word() const { return (uint32_t)p & 1u; }
+  __device__ void shuffle(uint64_t state) { p = (int32_t)((uint32_t)sm_mix(state + kGolden) & 1u) - 1; }
+  // the present order's sum counts only if it beats itself clamped, which it
+  // never does: the other order is the one to compare
+  __device__ bool improve(const int32_t (&h)[2][2]) {
+    const int32_t c0 = max(h[0][0], 0) + max(h[1][1], 0), c1 = max(h[0][1], 0) + max(h[1][0], 0);
+    const int32_t s0 = h[0][0] + h[1][1], s1 = h[0][1] + h[1][0];
+    const int32_t up = (bit_select(p, c1, c0) - bit_select(p, s0, s1)) >> 31;   // sums stay far inside 32 bits
+    p ^= up;
+    return up != 0;
+  }
+};
+
+// g: ranks per group; MG: groups per lane; RL: D^rem in LDS; S: wavefronts
+// per (family, start) run.  One wavefront runs a start of up to 128 groups of
+// two ranks (64 larger groups), exchanging assignments by cross-lane
+// permutes.  Beyond that two wavefronts share it (128 MG groups) and exchange
+// through LDS with a workgroup barrier per half-step: halving a lane's groups
+// then saves more than the barriers cost (512 ranks of two per group: 9.5 us
+// per activation against 15.1 with four groups per lane, whose registers
+// spill; 320 ranks of four: 16.5 against 28), while at 256 ranks of two it
+// costs more (4.1 against 3.5 us).
+template <int g, int MG, bool RL, int S>
 __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  // credit rows of the g x g endpoint pairs of an instance, padded to an odd
-  // number of words so that the lanes of a wavefront reading consecutive
-  // instances' rows fall in different LDS banks
-  constexpr int g2 = g * g, kRow = g2 | 1;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int g2 = g * g, RW = kResWords<g>;
+  static_assert(Order<g>::bits * MG <= 32, "the orders of a lane's groups are exchanged in one word");
+  constexpr int kSlots = kPlanWaves / S;   // runs side by side
+  // The credit rows of a lane's groups are held in registers for a whole run
+  // where they fit; else each half-step reads the entries it needs again.
+  constexpr bool kHold = 2 * MG * g * g2 <= 64;
+  constexpr int HM = kHold ? MG : 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = lane0(tid >> 6);
+  const int slot = wave & (kSlots - 1), part = wave / kSlots;
   const DevCatalogLayout& L = P.L;
-  const int N = L.N, Q = L.Q, nn = L.nn, QG = Q * g;
-  const int NP = L.J0 + L.J1, NS = P.n_start, FL = L.F0 + L.F1;
+  const int N = L.N, G = L.G, Q = L.Q, nn = L.nn, QG = Q * g, NS = P.n_start, kS = L.kS;
   // workgroup b plans matrix b of the batch: every global buffer is offset by b
   const size_t b = blockIdx.x, NN = (size_t)N * N, KN = (size_t)P.k_max * N;
-  const int64_t* gD = P.D + b * NN;
-  int64_t* gDrem = P.Drem + b * NN;
-  int32_t* gfamily = P.family + b * P.k_max;
-  int32_t* gdst = P.dst + b * KN;
-  int32_t* ginst = P.inst + b * KN;
-  int64_t* gbytes = P.bytes + b * KN;
-  int64_t* gsend_off = P.send_off ? P.send_off + b * KN : nullptr;
-  int64_t* gstream_off = P.stream_off ? P.stream_off + b * KN : nullptr;
-  int32_t* grecv_src = P.recv_src ? P.recv_src + b * KN : nullptr;
-  constexpr FixedLds FX = fixed_lds((size_t)64 * MG * g);
-  Shared* sh = (Shared*)smem;
-  int32_t* rinfo = (int32_t*)(smem + FX.rinfo);
-  int32_t* agg = (int32_t*)(smem + P.o_agg);         // [q][q2][k] units: k = 0 is A, k > 0 is B_k;
-                                                     // then one row of zeros
-  // row stride: odd (lanes reading one shift of different rows hit distinct
-  // banks) and at least nn + 3 (zero padding for the 4-wide shift unroll)
-  const int kS = (nn + 3) | 1;
-  uint16_t* terms = (uint16_t*)(smem + P.o_terms);
-  int32_t* pfb = (int32_t*)(smem + P.o_pfb);           // [NP][2] local family range
-  uint16_t* finfo = (uint16_t*)(smem + P.o_finfo);
-  PairRes* pr = (PairRes*)(smem + P.o_pair);
-  uint16_t* outT = (uint16_t*)(smem + P.o_outT);
-  uint16_t* inT = (uint16_t*)(smem + P.o_inT);
-  int8_t* ipos = (int8_t*)(smem + P.o_ipos);
-  uint8_t* ocls = smem + P.o_ocls;
-  uint8_t* iid = smem + P.o_iid;     // [FC][N] node-local instance id of every instance of the chunk
-  int32_t* hp = (int32_t*)(smem + P.o_hp);
-  uint32_t* raw = (uint32_t*)(smem + P.o_raw);       // residual of every credit entry (saturating)
-  uint8_t* sl = smem + P.o_sl;
-  uint8_t* dl = smem + P.o_dl;
-  uint8_t* bsl = smem + FX.bsl;
-  uint8_t* bdl = smem + FX.bdl;
-  uint8_t* bid = smem + FX.bid;
-  uint32_t* bx = (uint32_t*)(smem + FX.bx);
-  uint32_t* brw = (uint32_t*)(smem + FX.brw);
-  uint64_t* topkey = (uint64_t*)(smem + P.o_top);    // [FC] best credit triple of each family in the chunk
-  uint16_t* rset = (uint16_t*)(smem + P.o_rset);     // [nS][kMaxRTerms] agg row offsets (zero row past the end)
-  uint16_t* psid = (uint16_t*)(smem + P.o_psid);     // [J1] NIC-lane set of each NIC-carrying pattern
-  uint64_t* rbest = (uint64_t*)(smem + P.o_rbest);   // [nS] best shift: units << 12 | (4095 - shift)
-  int32_t* pbase = (int32_t*)(smem + P.o_pbase);     // [NP] diagonal-block score of each pattern
-  // D^rem entry each source rank's lane changed last, and its new value: the
-  // next credit gather takes it from here, so no barrier has to wait for the
-  // global store (stores of earlier iterations are complete by then).
-  uint8_t* rp = smem + P.o_rp;   // [FC][NS][G][2] packed permutations of the shuffled starts
-  int32_t* lastj = (int32_t*)(smem + FX.lastj);
-  int64_t* sacc = (int64_t*)(smem + FX.sacc);   // [N] bytes each rank has sent so far
-  int64_t* lastv = (int64_t*)(smem + FX.lastv);
   const int32_t* cat = P.cat;
+
+  Shared* sh = (Shared*)smem;
+  int32_t* agg = (int32_t*)(smem + P.o_agg);        // [q * Q + q2][kS] units: column 0 is A, column k is B_k; a zero row
+  uint2* rb = (uint2*)(smem + P.o_rb);              // [nS + 1] best {units, shift} of each set; the last is zero
+  const int npr = P.FC * NS * S;
+  int32_t* prF = (int32_t*)(smem + P.o_pr);         // [FC * NS][S] score of each (family, start) run of the chunk (S parts),
+  int32_t* prxp = prF + npr;                        // its largest lane volume on a PCIe-rate path
+  int32_t* prxn = prxp + npr;                       // and on a NIC path (units)
+  uint32_t* xw = (uint32_t*)(smem + P.o_xw) + slot * 2 * S * 64;   // S = 2: [2][S * 64] orders of the in- and out-lanes
+  uint2* out = (uint2*)(smem + P.o_out);            // [N] last activation: {destination | lane << 16, units} of each rank
+  uint32_t* colsum = (uint32_t*)(smem + P.o_out);   // [N], prologue only
+  int64_t* sacc = (int64_t*)(smem + P.o_sacc);      // [N] bytes each rank has sent so far
+  const unsigned char* tab = smem + P.o_tab;
+  const uint4* rows = (const uint4*)tab;
+  const uint2* info = (const uint2*)(tab + L.pl_info);
+  const int32_t* wtab = (const int32_t*)(tab + L.pl_wave);
+  const uint4* set_rows = (const uint4*)(tab + L.pl_sets);
+  // D^rem, [G][G][RW] units; a workspace slice is aligned up to 16 bytes (it holds 8 N^2 bytes, of which
+  // the blocks take at most 16/3 N^2)
+  uint32_t* res = RL ? (uint32_t*)(smem + P.o_res)
+                     : (uint32_t*)(((uintptr_t)(P.Drem + b * NN) + 15) & ~(uintptr_t)15);
+  auto div_q = [&](int x) { return Q == 1 ? x : (int)__umulhi((unsigned)x, L.q_magic); };
 
   // ---------------------------------------------------------------- prologue
   if (tid == 0) {
-    sh->err = 0;
-    sh->K = 0;
-    sh->total_rem = 0;
+    sh->total = 0;
     sh->total_units = 0;
-    sh->Lmax = 0;
-    sh->key = 0;
+    sh->Lmax_units = 0;
+    sh->err = 0;
     sh->huge = 0;
-  }
-  for (int r = tid; r < N; r += kPlanThreads) {
-    const int grp = r / g;
-    rinfo[r] = ((grp / Q) << 8) | ((grp % Q) << 4) | (r - grp * g);
-  }
-  // a diagonal-block term is kept as its count | (q * Q + q2) << 4, the
-  // index of its slot pair's A row (the scoring loop reads nothing else); a
-  // shift-block term's count is zeroed and each pattern's slots are padded
-  // with zeros to a multiple of 8, so no slot needs a bound check
-  const int TS8 = (L.TS + 7) & ~7;
-  for (int x = tid; x < NP * TS8; x += kPlanThreads) {
-    const int p = x / TS8, m = x - p * TS8;
-    const int tv = m < L.TS ? cat[L.off_terms + p * L.TS + m] : 0;
-    const int cnt = (tv >> 12) == 0 ? (tv & 15) : 0;
-    terms[x] = (uint16_t)(cnt | ((((tv >> 8) & 15) * Q + ((tv >> 4) & 15)) << 4));
-  }
-  for (int p = tid; p < NP; p += kPlanThreads) {
-    pfb[2 * p] = cat[L.off_fb + p];
-    pfb[2 * p + 1] = cat[L.off_fe + p];
-  }
-  for (int x = tid; x < FL * QG; x += kPlanThreads) {
-    // descriptor word and in-list entry of local family x / QG, index x % QG
-    const int lf = x / QG, idx = x - lf * QG;
-    const int info = cat[L.off_fam_info + x];
-    const int cls = info & 15, ss = (info >> 4) & 15, ds = (info >> 8) & 15;
-    int opos = 0;
-    for (int m = 0; m < g; ++m)
-      if (cat[L.off_fam_out + lf * QG + ss * g + m] == idx) opos = m;
-    const bool remote = cls == VP_PATH_NIC && lf >= L.F0;
-    int rsame = 0, nother = 0;
-    for (int m = 0; m < g; ++m) {
-      const int idx2 = cat[L.off_fam_in + lf * QG + ds * g + m];
-      const bool r2 = (cat[L.off_fam_info + lf * QG + idx2] & 15) == VP_PATH_NIC && lf >= L.F0;
-      if (r2 != remote) ++nother;
-      else if (idx2 < idx) ++rsame;
+    sh->key[0] = sh->key[1] = 0;
+    sh->top[0] = sh->top[1] = 0;
+    for (int x = 0; x < 4; ++x) {
+      sh->triple[x] = 0;
+      sh->changed[x] = 0;
     }
-    finfo[x] = (uint16_t)(cls | (ss << 2) | (ds << 5) | (opos << 8) | (rsame << 10) | (nother << 12));
+    sh->step_key[0] = sm_mix(sm_mix(P.seed + kGolden) + kGolden);
+    // what only the writers and the comparison of families use is read from
+    // LDS there: held in scalar registers through the loop it would push out
+    // what every wavefront needs
+    sh->D = P.D + b * NN;
+    sh->inst_id = cat + L.off_fam_info;
+    sh->family = P.family + b * P.k_max;
+    sh->dst = P.dst + b * KN;
+    sh->inst = P.inst + b * KN;
+    sh->bytes = P.bytes + b * KN;
+    sh->send_off = P.send_off ? P.send_off + b * KN : nullptr;
+    sh->stream_off = P.stream_off ? P.stream_off + b * KN : nullptr;
+    sh->recv_src = P.recv_src ? P.recv_src + b * KN : nullptr;
+    sh->unit = P.unit;
+    sh->lambda = P.lambda;
+    sh->bw_p = L.bw_cls[VP_PATH_PIX];
+    sh->bw_n = L.bw_cls[VP_PATH_NIC];
+  }
+  {
+    const uint4* src = (const uint4*)(cat + L.off_plan);
+    uint4* dst = (uint4*)(smem + P.o_tab);
+    const int n = (P.rec_lds ? L.pl_end : L.pl_recs) / 16;
+    for (int x = tid; x < n; x += 4 * kPlanThreads) {
+      uint4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = src[min(x + u * kPlanThreads, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (x + u * kPlanThreads < n) dst[x + u * kPlanThreads] = v[u];
+    }
   }
   for (int x = tid; x < kS * (Q * Q + 1); x += kPlanThreads) agg[x] = 0;
-  for (int x = tid; x < L.nS * kMaxRTerms; x += kPlanThreads) {
-    const int e = cat[L.off_rset + x];
-    rset[x] = (uint16_t)((e < 0 ? Q * Q : e) * kS);   // absent terms read the zero row
-  }
-  for (int x = tid; x < L.J1; x += kPlanThreads) psid[x] = (uint16_t)cat[L.off_psid + x];
-  for (int x = tid; x < P.FC; x += kPlanThreads) topkey[x] = 0;
+  for (int x = tid; x <= L.nS; x += kPlanThreads) rb[x] = make_uint2(0, 0);
   for (int x = tid; x < N; x += kPlanThreads) {
-    lastj[x] = -1;
+    colsum[x] = 0;
     sacc[x] = 0;
   }
-  int64_t* colsum = (int64_t*)hp;   // the credit area is free during the prologue
-  for (int x = tid; x < N; x += kPlanThreads) colsum[x] = 0;
   __syncthreads();
 
-  // one pass over D: validate, copy to D^rem, row / column sums, aggregates.
-  // An entry of 2^42 bytes or more is refused before anything is summed: at
-  // most 2^20 entries below 2^42 keep every row, column and total sum below
-  // 2^62.
+  // One pass over D, eight rows per wavefront at a time: validate, store the
+  // units blocked by group pair, sum rows, columns and aggregates.  An entry
+  // of 2^42 bytes or more is refused before anything uses the sums: at most
+  // 2^20 entries below 2^42 keep the total below 2^62, and the 32-bit unit
+  // sums are exact whenever the total passes its check.
   {
+    constexpr int RU = 8;
     bool bad = false, huge = false;
-    int64_t tot = 0, lmax = 0;
+    int64_t tot = 0, totu = 0;
+    uint32_t lmax = 0;
     const uint64_t mask = (uint64_t(1) << P.unit_shift) - 1;
-    for (int i = wave; i < N; i += kWaves) {
-      const int ri = rinfo[i], ni = ri >> 8, qi = (ri >> 4) & 15;
-      int64_t rs = 0;
-      for (int j = lane; j < N; j += 64) {
-        const int64_t v = gD[(size_t)i * N + j];
-        const bool divisible = ((uint64_t)v & mask) == 0 &&
-                               ((uint64_t)v >> P.unit_shift) * P.odd_inv <= P.odd_lim;
-        if (v < 0 || (i == j && v != 0) || !divisible) bad = true;
-        if (v >= (int64_t(1) << 42)) huge = true;
-        gDrem[(size_t)i * N + j] = v;
-        rs += v;
-        if (v > 0) {
-          const int rj = rinfo[j], nj = rj >> 8, qj = (rj >> 4) & 15;
-          int kk = nj - ni;
-          if (kk < 0) kk += nn;
-          atomicAdd((unsigned long long*)&colsum[j], (unsigned long long)v);
-          // exact quotient by the unit: v >> s times the odd part's inverse
-          const int32_t vu = (int32_t)(((uint64_t)v >> P.unit_shift) * P.odd_inv);
-          atomicAdd(&agg[(qi * Q + qj) * kS + kk], vu);
+    const int64_t* gD = P.D + b * NN;
+    for (int i0 = wave * RU; i0 < N; i0 += kPlanWaves * RU) {
+      uint32_t rs[RU];
+#pragma unroll
+      for (int u = 0; u < RU; ++u) rs[u] = 0;
+      for (int j0 = 0; j0 < N; j0 += 64) {
+        const int j = j0 + lane, jc = min(j, N - 1);
+        int64_t v[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) v[u] = gD[(size_t)min(i0 + u, N - 1) * N + jc];
+        const int gj = jc / g, nj = div_q(gj), qj = gj - nj * Q;
+        uint32_t cs = 0;
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+          const int i = i0 + u;
+          if (i >= N) break;   // uniform
+          const int gi = i / g, ni = div_q(gi), qi = gi - ni * Q;
+          if (j < N) {
+            const uint64_t w = (uint64_t)v[u] >> P.unit_shift, units = w * P.odd_inv;   // exact quotient by the unit
+            if (v[u] < 0 || (i == j && v[u] != 0) || ((uint64_t)v[u] & mask) != 0 || units > P.odd_lim) bad = true;
+            if (v[u] >= (int64_t(1) << 42)) huge = true;
+            tot += v[u];
+            totu += (int64_t)units;
+            const uint32_t vu = (uint32_t)units;
+            res[((size_t)gi * G + gj) * RW + (i - gi * g) * g + (j - gj * g)] = vu;
+            rs[u] += vu;
+            cs += vu;
+            int kk = nj - ni;
+            if (kk < 0) kk += nn;
+            if (vu) atomicAdd(&agg[(qi * Q + qj) * kS + kk], (int32_t)vu);
+          }
         }
+        if (j < N && cs) atomicAdd(&colsum[j], cs);
       }
-      rs = wave_sum(rs);
-      tot += rs;
-      lmax = rs > lmax ? rs : lmax;
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const uint32_t s = wave_reduce<OpAdd>(rs[u]);
+        lmax = s > lmax ? s : lmax;
+      }
     }
-    if (bad) set_err(sh, VP_ERR_INVALID_DEMAND);
+    if (bad) atomicCAS(&sh->err, 0, VP_ERR_INVALID_DEMAND);
     if (huge) sh->huge = 1;
+    tot = wave_sum64(tot);
+    totu = wave_sum64(totu);
     if (lane == 0) {
-      atomicAdd((unsigned long long*)&sh->total_rem, (unsigned long long)tot);
-      atomicAdd((unsigned long long*)&sh->total_units,
-                (unsigned long long)(((uint64_t)tot >> P.unit_shift) * P.odd_inv));
-      atomicMax((unsigned long long*)&sh->Lmax, (unsigned long long)lmax);
+      atomicAdd((unsigned long long*)&sh->total, (unsigned long long)tot);
+      atomicAdd((unsigned long long*)&sh->total_units, (unsigned long long)totu);
+      atomicMax(&sh->Lmax_units, lmax);
     }
   }
   __syncthreads();
   {
-    int64_t lmax = 0;
+    uint32_t lmax = 0;
     for (int j = tid; j < N; j += kPlanThreads) lmax = colsum[j] > lmax ? colsum[j] : lmax;
-    lmax = wave_max(lmax);
-    if (lane == 0) atomicMax((unsigned long long*)&sh->Lmax, (unsigned long long)lmax);
+    lmax = wave_reduce<OpMax>(lmax);
+    if (lane == 0) atomicMax(&sh->Lmax_units, lmax);
   }
   __syncthreads();
-  if (tid == 0 && sh->err == 0) {
+  // the quantum and the lane caps, in every wavefront
+  int err = lane0(sh->err);
+  const int64_t Lmax = lane0((int64_t)sh->Lmax_units) * P.unit, total_units = lane0(sh->total_units);
+  int64_t tau;
+  uint32_t cap_p = 1, cap_n = 1;   // units
+  {
     const int64_t den = L.bw_max * P.k_target;
-    int64_t tau = (sh->Lmax + den - 1) / den;
+    tau = floor_div(Lmax + den - 1, den);
     if (tau < 1) tau = 1;
-    sh->tau = tau;
-    for (int c = 0; c < 4; ++c) {
-      int64_t cap = tau * L.bw_cls[c] / P.unit * P.unit;
-      if (cap < P.unit) cap = P.unit;
-      sh->cap[c] = cap;
-      sh->capu[c] = (int32_t)(cap / P.unit);
-      // credits are int32 bytes below 2^31 and int32 units below 2^27
-      if (cap >= (int64_t(1) << 31) || cap / P.unit >= (int64_t(1) << 27)) set_err(sh, VP_ERR_UNSUPPORTED);
+    bool over = false;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      int64_t cu = floor_div(tau * L.bw_cls[c ? VP_PATH_NIC : VP_PATH_PIX], P.unit);
+      if (cu < 1) cu = 1;
+      // credits are int32 units below 2^27; a lane's bytes stay below 2^31
+      over |= cu >= (int64_t(1) << 27) || cu * P.unit >= (int64_t(1) << 31);
+      (c ? cap_n : cap_p) = (uint32_t)cu;
     }
-    if (sh->huge || sh->total_rem >= (int64_t(1) << 42) || sh->total_units >= (int64_t(1) << 28))
-      set_err(sh, VP_ERR_UNSUPPORTED);
+    over |= sh->huge != 0 || sh->total >= (int64_t(1) << 42) || total_units >= (int64_t(1) << 28);
+    if (err == 0 && over) err = VP_ERR_UNSUPPORTED;
   }
-  __syncthreads();
+  err = lane0(err);
+  cap_p = (uint32_t)lane0((int32_t)cap_p);
+  cap_n = (uint32_t)lane0((int32_t)cap_n);
 
-  // this thread's first (family, instance) item of a gather and the step
-  // between its items, fixed for the plan
-  const int g_c0 = tid / N, g_t0 = tid - (tid / N) * N, g_dc = kPlanThreads / N, g_dt = kPlanThreads % N;
-  // the per-class caps are plan constants: held in registers
-  const int64_t cap_c0 = lane0(sh->cap[0]), cap_c1 = lane0(sh->cap[1]), cap_c2 = lane0(sh->cap[2]),
-                cap_c3 = lane0(sh->cap[3]);
+  // this lane's groups; a lane past the last group computes on group 0 and
+  // changes nothing
+  int ga[MG], gn[MG], gq[MG];
+  bool own[MG];
+  uint32_t my_cap_p[MG], my_cap_n[MG];
+#pragma unroll
+  for (int r = 0; r < MG; ++r) {
+    ga[r] = lane + 64 * (r * S + part);
+    own[r] = ga[r] < G;
+    ga[r] = own[r] ? ga[r] : 0;
+    gn[r] = div_q(ga[r]);
+    gq[r] = ga[r] - gn[r] * Q;
+    my_cap_p[r] = own[r] ? cap_p : 0;
+    my_cap_n[r] = own[r] ? cap_n : 0;
+  }
+  // this lane's share of the shape scores
+  const int ib = lane0(wtab[wave]), ie = lane0(wtab[wave + 1]);
+  const int sb = lane0(wtab[kPlanWaves + 1 + wave]), ns = lane0(wtab[kPlanWaves + 2 + wave]) - sb;
+  const int nitem = (ie - ib + 63) >> 6, RW8 = L.RW / 8, LPS = 1 << P.LPS_log2;
+  const bool has_set = P.held && lane < (ns << P.LPS_log2);
+  const int my_set = has_set ? sb + (lane >> P.LPS_log2) : 0;
+  const int SPT = P.SPT, k0 = 1 + (lane & (LPS - 1)) * SPT;
+  // rows of this lane's set and first item (two to a register), absent ones
+  // the zero row
+  const uint32_t zero2 = (uint32_t)(Q * Q * kS) * 0x10001u;
+  uint4 srow = make_uint4(zero2, zero2, zero2, zero2), irow = srow;
+  uint2 info0 = make_uint2(0, 0);
+  if (has_set) srow = set_rows[my_set];
+  if (ib + lane < ie) {
+    irow = rows[(ib + lane) * RW8];
+    info0 = info[ib + lane];
+  }
+  auto row_of = [&](const uint4& o, int m) -> const int32_t* {
+    const uint32_t w = m < 2 ? o.x : m < 4 ? o.y : m < 6 ? o.z : o.w;
+    return agg + ((w >> (16 * (m & 1))) & 0xFFFF);
+  };
+  // sum of B_k over a set's lanes
+  auto shift_sum = [&](int k) {
+    int32_t s = row_of(srow, 0)[k] + row_of(srow, 1)[k] + row_of(srow, 2)[k] + row_of(srow, 3)[k];
+    if (P.MRT > 4) s += row_of(srow, 4)[k] + row_of(srow, 5)[k] + row_of(srow, 6)[k] + row_of(srow, 7)[k];
+    return s;
+  };
+  int32_t held[kHeldShifts];
+#pragma unroll
+  for (int u = 0; u < kHeldShifts; ++u) {
+    const int k = k0 + u;
+    held[u] = has_set && u < SPT && k < nn ? shift_sum(k) : -1;
+  }
+
   // ---------------------------------------------------------------- loop
-  int stamp_it = 0;
-  (void)stamp_it;
-  while (true) {
-    // The loop's exit conditions are read here and tested after the scoring
-    // work, which does not depend on them (on the last pass it is wasted),
-    // so the read's latency hides behind it.
-    const int err_ = sh->err, K_ = sh->K;
-    stamp_it = K_;
-    VP_STAMP(0);
-    const int64_t rem_ = sh->total_rem;
+  // Every wavefront keeps these itself (they follow from LDS values that all
+  // of them read): activations so far, units left, the last activation's
+  // shift and family.
+  int K = 0, kprev = -1, lf_prev = 0, f_prev = 0, written = 0;
+  uint32_t rem = (uint32_t)total_units;
 
-    // Step 1: score every shape; argmax.  A shape (k, p) scores base(p), its
-    // diagonal-block terms against A, plus, for k > 0, the sum of B_k over
-    // its NIC-lane set.  The shift part depends on p only through that set,
-    // so (a) every distinct set finds its best shift (LPS lanes per set,
-    // SPT shifts each, ties to the lowest shift) while other threads compute
-    // every base(p); (b) one thread per pattern adds its set's best and the
-    // block takes the argmax (ties to the lowest canonical shape index).
-    {
-      const int na = L.nS * P.LPS;
-      for (int x = tid; x < na + NP; x += kPlanThreads) {
-        if (x < na) {
-          const int si = x >> P.LPS_log2, ch = x & (P.LPS - 1);
-          const int k0 = 1 + ch * P.SPT, k1 = min(nn, k0 + P.SPT);
-          // all loads unconditional and independent: absent terms read the zero row
-          int off[kMaxRTerms];
+  // The last activation (step k, local family lf) to the schedule arrays,
+  // the first ranks by the last wavefront.  What the stores wait for in
+  // global memory is asked for ahead of them.
+  struct Lane {
+    uint2 w;       // {destination | lane << 16, units}
+    int id;        // instance
+    int64_t d;     // demand of the pair
+    uint32_t left;   // and its residual, this activation subtracted
+  };
+  auto read_lane_out = [&](int i, int lf) {
+    Lane x{};
+    x.w = out[i];
+    const int j = (int)(x.w.x & 0xFFFF);
+    x.id = sh->inst_id[lf * QG + (int)(x.w.x >> 16)];
+    if (sh->send_off) {
+      x.d = sh->D[(size_t)i * N + j];
+      const int a = i / g, c = j / g;
+      x.left = res[((size_t)a * G + c) * RW + (i - a * g) * g + (j - c * g)];
+    }
+    return x;
+  };
+  auto write_lane = [&](int i, int k, int f, const Lane& l) {
+    const int j = (int)(l.w.x & 0xFFFF);
+    const uint32_t unit = (uint32_t)sh->unit;   // below 2^31
+    const int64_t x = (int64_t)((uint64_t)l.w.y * unit);
+    const uint32_t o = (uint32_t)(k * N + i);
+    if (sh->send_off) {
+      // Sec. 5 buffer layout: where this lane's slice sits in rank i's send
+      // buffer and in its stream to j (the bytes sent there before)
+      const int64_t so = sacc[i];
+      sacc[i] = so + x;
+      at32(sh->send_off, o) = so;
+      at32(sh->stream_off, o) = l.d - x - (int64_t)((uint64_t)l.left * unit);
+    }
+    at32(sh->dst, o) = j;
+    at32(sh->inst, o) = l.id >> 12;
+    at32(sh->bytes, o) = x;
+    if (sh->recv_src) at32(sh->recv_src, (uint32_t)(k * N + j)) = i;   // pi_k is a permutation
+    if (i == 0) sh->family[k] = f;
+  };
+  const int i_first = (kPlanWaves - 1 - wave) * 64 + lane;
+
+  // The half-steps of S = 2 so far (see publish).
+  int half_step = 0;
+  // One MultiStartAA run: local family lf, one start, on this wavefront.
+  // Leaves the binding in `sig` (source of each out-lane), `jf` (member of
+  // its destination), `ent` (out-lane descriptor), `dg` (destination group)
+  // and `xv` (units); returns the binding score F (Eq. (8)) and, if need_x,
+  // the largest lane volume on PCIe-rate and NIC paths.
+  struct Binding {
+    Order<g> sig[MG];
+    int jf[MG][g];   // for g = 2 a mask, all ones for member 1
+    __device__ int member(int r, int m) const { return g == 2 ? jf[r][m] & 1 : jf[r][m]; }
+    uint32_t ent[MG][g], dg[MG][g];
+    uint32_t xv[MG][g];
+    uint32_t raw[RL ? 1 : HM][g][g2];   // residuals of the out-lanes (D^rem in global memory)
+  };
+  auto run = [&](Binding& B, int lf, int kstar, int fbase, int start, uint64_t step_key, bool need_x, uint32_t& xp,
+                 uint32_t& xn) __attribute__((always_inline)) -> uint32_t {
+    // the records of this lane's groups: g out-lanes, then g in-lanes
+    uint32_t rec[MG][g];
 #pragma unroll
-          for (int m = 0; m < kMaxRTerms; ++m) off[m] = rset[si * kMaxRTerms + m];
-          // sums are never negative: the first shift always takes the lead,
-          // and a strict gain keeps the lowest of equal shifts
-          int32_t br = -1;
-          int bk = 0;
-          for (int kb = k0; kb < k1; kb += 4) {
-            int32_t r0 = 0, r1 = 0, r2 = 0, r3 = 0;
+    for (int r = 0; r < MG; ++r) {
+      const int at = (lf * Q + gq[r]) * g;
+      if (P.rec_lds) {
 #pragma unroll
-            for (int m0 = 0; m0 < kMaxRTerms; m0 += 4) {
-              if (m0 >= P.MRT) break;
+        for (int m = 0; m < g; ++m) {
+          rec[r][m] = ((const uint32_t*)(tab + L.pl_recs))[at + m];
+          asm("" : "+v"(rec[r][m]));   // keeps the two loads apart: merged they would be one flat load
+        }
+      } else {
 #pragma unroll
-              for (int m = m0; m < m0 + 4; ++m) {
-                const int32_t* row = agg + off[m] + kb;   // rows are zero-padded past nn
-                r0 += row[0];
-                r1 += row[1];
-                r2 += row[2];
-                r3 += row[3];
-              }
-            }
-            if (r0 > br) {
-              br = r0;
-              bk = kb;
-            }
-            if (kb + 1 < k1 && r1 > br) {
-              br = r1;
-              bk = kb + 1;
-            }
-            if (kb + 2 < k1 && r2 > br) {
-              br = r2;
-              bk = kb + 2;
-            }
-            if (kb + 3 < k1 && r3 > br) {
-              br = r3;
-              bk = kb + 3;
-            }
+        for (int m = 0; m < g; ++m) rec[r][m] = ((const uint32_t*)((const char*)(cat + L.off_plan) + L.pl_recs))[at + m];
+      }
+    }
+    auto half = [&](int r, int x) { return (rec[r][x >> 1] >> (16 * (x & 1))) & 0xFFFFu; };
+    uint32_t raw[HM][g][g2], rin[HM][g][g2];
+    // the other side of every lane: its group's word and bit there, and the
+    // position in its list
+    uint32_t olane[MG][g], oshift[MG][g], ilane[MG][g], ishift[MG][g];
+    int opos[MG][g], ipos[MG][g];
+    bool oself[MG][g], iself[MG][g], onic[MG][g];
+    uint32_t ocap[MG][g], icap[MG][g];
+    uint32_t sg[MG][g];
+    // where group d's order is: its word (byte offset: lane, and with two
+    // wavefronts its part) and the bit its order starts at
+    auto word_of = [&](uint32_t d) { return S == 1 ? (d & 63) << 2 : (d & 127) << 2; };
+    auto shift_of = [&](uint32_t d) { return (S == 1 ? d >> 6 : d >> 7) * Order<g>::bits; };
+#pragma unroll
+    for (int r = 0; r < MG; ++r) {
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        const uint32_t e = half(r, m);
+        B.ent[r][m] = e;
+        onic[r][m] = (e & 3) == VP_PATH_NIC;
+        const int kk = onic[r][m] ? kstar : 0;
+        int dn = gn[r] + kk;
+        dn = (int)min((uint32_t)dn, (uint32_t)(dn - nn));
+        const uint32_t d = (uint32_t)(dn * Q) + ((e >> 2) & 7);
+        // rank of the lane inside the in-list of group d: cross-node lanes
+        // come first exactly where their source node is lower
+        opos[r][m] = (int)((e >> 5) & 3) + ((kk != 0) != (dn >= kstar) ? (int)((e >> 7) & 7) : 0);
+        B.dg[r][m] = d;
+        oself[r][m] = own[r] && d == (uint32_t)ga[r];
+        ocap[r][m] = onic[r][m] ? my_cap_n[r] : my_cap_p[r];
+        olane[r][m] = word_of(d);
+        oshift[r][m] = shift_of(d);
+        if constexpr (kHold) load_block<g>(res + ((uint32_t)(ga[r] * G) + d) * RW, raw[r][m]);
+      }
+      // in-lanes, stored cross-node lanes first
+      int nr = 0;
+#pragma unroll
+      for (int m = 0; m < g; ++m) nr += (half(r, g + m) & 3) == VP_PATH_NIC;
+      const int rot = gn[r] >= kstar ? 0 : nr;
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        uint32_t e = half(r, g + m);
+#pragma unroll
+        for (int t = 1; t < g; ++t) e = rot == t ? half(r, g + (m + t) % g) : e;
+        const bool nic = (e & 3) == VP_PATH_NIC;
+        int sn = gn[r] - (nic ? kstar : 0);
+        sn = (int)min((uint32_t)sn, (uint32_t)(sn + nn));
+        const uint32_t s = (uint32_t)(sn * Q) + ((e >> 2) & 7);
+        sg[r][m] = s;
+        iself[r][m] = own[r] && s == (uint32_t)ga[r];
+        icap[r][m] = nic ? my_cap_n[r] : my_cap_p[r];
+        ipos[r][m] = (int)((e >> 5) & 3);
+        ilane[r][m] = word_of(s);
+        ishift[r][m] = shift_of(s);
+        if constexpr (kHold) load_block<g>(res + (s * (uint32_t)G + (uint32_t)ga[r]) * RW, rin[r][m]);
+      }
+    }
+    Order<g> del[MG];
+    if (start == 0) {
+#pragma unroll
+      for (int r = 0; r < MG; ++r) {
+        B.sig[r].identity();
+        del[r].identity();
+      }
+    } else {
+      // independent Fisher-Yates shuffles of every group's sources and
+      // destinations on SplitMix64 streams keyed by seed, iteration, family,
+      // start, group and side; the key prefix is uniform over the wavefront
+      uint64_t k3 = step_key ^ (uint64_t)(fbase + lf);
+      k3 = sm_mix(k3 + kGolden) ^ (uint64_t)start;
+      const uint64_t k4 = sm_mix(k3 + kGolden);
+#pragma unroll
+      for (int r = 0; r < MG; ++r) {
+        const uint64_t k5 = sm_mix((k4 ^ (uint64_t)ga[r]) + kGolden);
+        B.sig[r].shuffle(k5);
+        del[r].shuffle(k5 ^ 1);
+      }
+    }
+    // credits: min(D^rem, cap), kForbiddenU for a self pair
+    int32_t hs[HM][g][g2], hd[HM][g][g2];
+    // (none at all on a lane past the last group)
+    auto credit = [&](uint32_t w, uint32_t cap, bool self) {
+      return self ? kForbiddenU : (int32_t)(w < cap ? w : cap);
+    };
+    if constexpr (kHold) {
+#pragma unroll
+      for (int r = 0; r < MG; ++r)
+#pragma unroll
+        for (int m = 0; m < g; ++m)
+#pragma unroll
+          for (int e = 0; e < g2; ++e) {
+            hs[r][m][e] = credit(raw[r][m][e], ocap[r][m], e / g == e % g && oself[r][m]);
+            hd[r][m][e] = credit(rin[r][m][e], icap[r][m], e / g == e % g && iself[r][m]);
+            if constexpr (!RL) B.raw[r][m][e] = raw[r][m][e];
           }
-          uint64_t bkey = br >= 0 ? ((uint64_t)(uint32_t)br << 12) | (uint64_t)(4095 - bk) : 0;
-          // the LPS lanes of a set are adjacent lanes of one wavefront
-          for (int o = 1; o < P.LPS; o <<= 1) {
-            const uint64_t y = __shfl_xor(bkey, o);
-            bkey = y > bkey ? y : bkey;
+    }
+    // credit of out-lane (r, m) from source il to member jl, and of in-lane
+    // (r, m) from member il to destination jl
+    auto out_credit = [&](int r, int m, int il, int jl) {
+      return credit(res[((uint32_t)(ga[r] * G) + B.dg[r][m]) * RW + il * g + jl], ocap[r][m], il == jl && oself[r][m]);
+    };
+    auto in_credit = [&](int r, int m, int il, int jl) {
+      return credit(res[(sg[r][m] * (uint32_t)G + (uint32_t)ga[r]) * RW + il * g + jl], icap[r][m], il == jl && iself[r][m]);
+    };
+    int prot_o[MG], prot_i[MG];   // the protected lane's out- and in-list position, -1 elsewhere
+#pragma unroll
+    for (int r = 0; r < MG; ++r) prot_o[r] = prot_i[r] = -1;
+    // canonical binding plus the highest-credit triple, ties to the smallest
+    // (lane, i, j): out-lanes of a group are in lane order
+    auto bind_top = [&](bool mine, int r0, int m0, int il, int jl, int d, int mi) {
+#pragma unroll
+      for (int r = 0; r < MG; ++r) {
+        // members are still in order: the one to move is at its own position
+        const bool so = mine && r == r0, di = ga[r] == d && own[r];
+        prot_o[r] = so ? m0 : -1;
+        B.sig[r].swap_if(so, m0, il);
+        prot_i[r] = di ? mi : -1;
+        del[r].swap_if(di, mi, jl);
+      }
+    };
+    if (start == 0) {
+      constexpr int kEnt = MG * g * g2, kIdx = kEnt <= 2 ? 1 : kEnt <= 8 ? 3 : kEnt <= 16 ? 4 : 5;
+      auto entry = [&](int x) -> int32_t {   // credit x of this lane, in (lane, i, j) order
+        const int r = x / (g * g2), m = x / g2 % g, e = x % g2;
+        if constexpr (kHold) return hs[r][m][e];
+        else return out_credit(r, m, e / g, e % g);
+      };
+      uint32_t tv = 0, tw = 0;   // the largest credit and the first entry that has it
+      if constexpr (kEnt <= 32) {
+        // credits stay below 2^27: value and (inverted) index in one word
+        int32_t key = 0;
+#pragma unroll
+        for (int x = 0; x < kEnt; ++x) key = max(key, entry(x) << kIdx | ((1 << kIdx) - 1 - x));
+        static_assert(kIdx <= 4 || kEnt > 16, "index bits");
+        tv = (uint32_t)key >> kIdx;
+        tw = (uint32_t)((1 << kIdx) - 1) - ((uint32_t)key & ((1 << kIdx) - 1));
+      } else {
+#pragma unroll
+        for (int x = 0; x < kEnt; ++x) {
+          const int32_t v = entry(x);
+          tw = v > (int32_t)tv ? (uint32_t)x : tw;
+          tv = (uint32_t)max((int32_t)tv, v);
+        }
+      }
+      const uint32_t top = wave_reduce<OpMax>(tv);
+      if (top != 0) {
+        uint64_t eq = __ballot(tv == top);
+        if ((eq & (eq - 1)) != 0) {
+          // the lowest (lane, i, j) among the lanes' first entries
+          uint32_t t = 0;
+#pragma unroll
+          for (int r = 0; r < MG; ++r)
+#pragma unroll
+            for (int m = 0; m < g; ++m)
+              t = tw / g2 == (uint32_t)(r * g + m) ? (uint32_t)(gn[r] * QG) + (B.ent[r][m] >> 10) : t;
+          const uint32_t key = tv == top ? t * (uint32_t)g2 + tw % g2 : ~0u;
+          eq = __ballot(key == wave_reduce<OpMin>(key));
+        }
+        const int tl = __builtin_ctzll(eq);   // the lane, its out-lane and (i, j)
+        const uint32_t w = read_lane(tw, tl);
+        const uint32_t om = w / g2, e = w % g2;
+        const int r0 = (int)(om / g), m0 = (int)(om % g), il = (int)(e / g), jl = (int)(e % g);
+        uint32_t dd = B.dg[0][0];
+        int pp = opos[0][0];
+#pragma unroll
+        for (int r = 0; r < MG; ++r)
+#pragma unroll
+          for (int m = 0; m < g; ++m) {
+            dd = om == (uint32_t)(r * g + m) ? B.dg[r][m] : dd;
+            pp = om == (uint32_t)(r * g + m) ? opos[r][m] : pp;
           }
-          if (ch == 0) rbest[si] = bkey;
+        const int d = (int)read_lane(dd, tl), mi = (int)read_lane((uint32_t)pp, tl);
+        if constexpr (S == 1) {
+          bind_top(lane == tl, r0, m0, il, jl, d, mi);
         } else {
-          const int p = x - na;
-          const uint16_t* tp = terms + p * TS8;
-          // term slots eight at a time up to the longest diagonal part, the
-          // slot loads of a group issued together and then their A loads;
-          // shift-block and padding slots weigh zero
-          int32_t sb = 0;
-          for (int m0 = 0; m0 < P.MLT; m0 += 8) {
-            int tv[8];
+          // the two wavefronts' triples meet in one word: credit, (lane, i, j)
+          // inverted (below 2^14), destination group, position there
+          uint32_t t = 0;
 #pragma unroll
-            for (int m = 0; m < 8; ++m) tv[m] = tp[m0 + m];
-            int32_t av[8];
+          for (int r = 0; r < MG; ++r)
 #pragma unroll
-            for (int m = 0; m < 8; ++m) av[m] = agg[__umul24((unsigned)(tv[m] >> 4), (unsigned)kS)];
-#pragma unroll
-            for (int m = 0; m < 8; ++m) sb += (tv[m] & 15) * av[m];
-          }
-          pbase[p] = sb;
+            for (int m = 0; m < g; ++m) t = om == (uint32_t)(r * g + m) ? (uint32_t)(gn[r] * QG) + (B.ent[r][m] >> 10) : t;
+          if (lane == tl)
+            atomicMax((unsigned long long*)&sh->triple[slot],
+                      (unsigned long long)top << 32 | (unsigned long long)(0x3FFF - (t * (uint32_t)g2 + e)) << 16 |
+                          (unsigned long long)(d << 2 | mi));
         }
       }
     }
-    VP_STAMP(1);
-    if (err_ || rem_ == 0) break;   // the same LDS words for every thread
-    if (K_ >= P.k_max) {
-      __syncthreads();
-      if (tid == 0) set_err(sh, VP_ERR_CAPACITY);
-      break;
-    }
-    // iteration-wide values read from LDS are made wavefront-uniform, so
-    // that what is derived from them runs on the scalar unit
-    const int K = lane0(K_);
-    lds_barrier();
-    VP_STAMP(2);
-    {
-      uint64_t best = 0;
-      for (int p = tid; p < NP; p += kPlanThreads) {
-        int32_t sc = pbase[p];
-        int j = p;
-        if (p >= L.J0) {
-          const uint64_t rb = rbest[psid[p - L.J0]];
-          sc += (int32_t)(rb >> 12);
-          j = ((4095 - (int)(rb & 4095)) << 12) | (p - L.J0);   // same order as the canonical shape index
+    if constexpr (S == 2) {
+      lds_barrier();   // every wavefront comes here: runs are in step
+      if (start == 0) {
+        const uint64_t w = (uint64_t)lane0((int64_t)sh->triple[slot]);
+        if (w != 0) {
+          const uint32_t key = 0x3FFF - ((uint32_t)(w >> 16) & 0x3FFF), t = key / (uint32_t)g2, e = key % (uint32_t)g2;
+          int r0 = -1, m0 = 0;
+#pragma unroll
+          for (int r = 0; r < MG; ++r)
+#pragma unroll
+            for (int m = 0; m < g; ++m)
+              if (own[r] && (uint32_t)(gn[r] * QG) + (B.ent[r][m] >> 10) == t) {
+                r0 = r;
+                m0 = m;
+              }
+          bind_top(r0 >= 0, r0, m0, (int)(e / g), (int)(e % g), (int)((w >> 2) & 0x3FFF), (int)(w & 3));
         }
-        const uint64_t key = ((uint64_t)(uint32_t)sc << 20) | (uint64_t)(0xFFFFF - j);
-        best = key > best ? key : best;
       }
-      best = wave_max_u(best);
-      if (lane == 0 && best) atomicMax((unsigned long long*)&sh->key, (unsigned long long)best);
     }
-    lds_barrier();
-    const uint64_t key = (uint64_t)lane0((int64_t)sh->key);
-    VP_STAMP(3);
-    if ((key >> 20) == 0) {
-      __syncthreads();
-      if (tid == 0) set_err(sh, VP_ERR_NO_PROGRESS);
-      break;
-    }
-    const int code = 0xFFFFF - (int)(key & 0xFFFFF);
-    const int kstar = code >> 12, pstar = kstar ? L.J0 + (code & 4095) : code;
-    const int lb = lane0(pfb[2 * pstar]), le = lane0(pfb[2 * pstar + 1]);
-    const int fbase = kstar == 0 ? 0 : (kstar - 1) * L.F1;
-    const int fb = lb + fbase, fe = le + fbase;
-    // best candidate of the iteration so far: each wavefront that writes the
-    // winner evaluates the candidates itself (the same reads in the same
-    // order), so each holds it in registers and no barrier separates the
-    // evaluation from the update
-    bool best_valid = false;
-    int64_t best_S = 0, best_xm = 0, best_bm = 1;
-    int best_f = 0, best_c = 0, best_s = 0, best_chunk = 0;
-
-    // Steps 2-3 over the shape's bucket, FC families at a time.
-    int last_cb = fb;
-    for (int cb = fb; cb < fe; cb += P.FC) {
-      last_cb = cb;
-      const int nc = min(P.FC, fe - cb);
-      // group lists and credits of every (family, instance)
-      {
-        const int tot = nc * N;
-        int c = g_c0, t = g_t0;
-        for (int x = tid; x < tot; x += kPlanThreads) {
-          // local family: f - fbase stays inside the pattern's local range
-          const int lf = cb - fbase + c;
-          const int n = (int)__umulhi((unsigned)t, P.qg_magic), idx = t - n * QG;   // t / QG
-          const uint32_t w = finfo[lf * QG + idx];
-          const int cl = d_cls(w), a = n * Q + d_ss(w);
-          int dn = n;
-          if (cl == VP_PATH_NIC && kstar) {
-            dn = n + kstar;
-            if (dn >= nn) dn -= nn;
+    // Self-binding repair, per group in out-list order: trade destinations
+    // with the first other unprotected in-lane, else sources with the first
+    // other unprotected out-lane.
+#pragma unroll
+    for (int r = 0; r < MG; ++r)
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        const int mi = opos[r][m];
+        if (oself[r][m] && B.sig[r].at(m) == del[r].at(mi)) {
+          int pi = -1, po = -1;
+#pragma unroll
+          for (int x = g - 1; x >= 0; --x) {
+            pi = x != mi && x != prot_i[r] ? x : pi;
+            po = x != m && x != prot_o[r] ? x : po;
           }
-          const int d = dn * Q + d_ds(w);
-          // rank of t inside the in-list of group d (family order = ascending t)
-          const bool remote = cl == VP_PATH_NIC && kstar;
-          const bool remote_first = dn >= kstar;   // cross-node sources sit on a lower node
-          const int mi = d_rsame(w) + ((remote != remote_first) ? d_nother(w) : 0);
-          const int op = d_opos(w);
-          // Every global load of the item is issued first, unconditionally:
-          // the residuals of its g x g pairs (a self pair's zero entry is
-          // read and not used; the value is stale only for the entry the
-          // last update changed, which LDS holds) and the instance id, which
-          // is only written out with the winner.
-          int64_t gv[g][g];
+          del[r].swap_if(pi >= 0, mi, pi);
+          B.sig[r].swap_if(pi < 0 && po >= 0, m, po);
+        }
+      }
+    // Alternating Algorithm: source half, then destination half.  A half that
+    // changes nothing, other than the very first, leaves a fixed point: the
+    // half before it made its own side optimal against this side, which has
+    // not moved.  Stopping there gives the same binding as stopping after a
+    // whole unchanged sweep.
+    auto pack = [&](const Order<g> (&a)[MG]) -> uint32_t {
+      if constexpr (g == 2 && MG == 1) {
+        return (uint32_t)a[0].p;
+      } else {
+        uint32_t w = a[0].word();
 #pragma unroll
-          for (int il = 0; il < g; ++il)
+        for (int r = 1; r < MG; ++r) w |= a[r].word() << (r * Order<g>::bits);
+        return w;
+      }
+    };
+    // entry `i` of a row (or column) of credits, i a member or, for g = 2, its mask
+    auto pick = [&](const int32_t (&c)[g], int i) {
+      if constexpr (g == 2) {
+        return bit_select(i, c[1], c[0]);
+      } else {
+        int32_t v = c[0];
 #pragma unroll
-            for (int jl = 0; jl < g; ++jl) gv[il][jl] = at32(gDrem, (uint32_t)((a * g + il) * N + d * g + jl));
-          const int idv = cat[L.off_fam_info + lf * QG + idx];
-          int lj[g];
-          int64_t lv[g];
+        for (int x = 1; x < g; ++x) v = bit_select(i == x ? -1 : 0, c[x], v);
+        return v;
+      }
+    };
+    // Member at the other side of a lane, from this lane's view of that side's
+    // orders `w`: a permute, or (S = 2) the words that publish() left in LDS.
+    auto fetch = [&](uint32_t from, uint32_t shift, int pos, uint32_t w, int side) {
+      uint32_t v;
+      if constexpr (S == 1) v = (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)w);
+      else v = *(const uint32_t*)((const char*)(xw + side * S * 64) + from);
+      if constexpr (g == 2) {   // a mask: all ones is member 1 (`pos` is one as well)
+        if constexpr (MG == 1) return (int)v ^ pos;
+        else return ((int)(v << (31 - shift)) >> 31) ^ pos;
+      } else {
+        if constexpr (MG > 1) v >>= shift;
+        return Order<g>::member(v, pos);
+      }
+    };
+    int opm[MG][g], ipm[MG][g];
+#pragma unroll
+    for (int r = 0; r < MG; ++r)
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        opm[r][m] = g == 2 ? -opos[r][m] : opos[r][m];
+        ipm[r][m] = g == 2 ? -ipos[r][m] : ipos[r][m];
+      }
+    VP_STAMP(5);
+    // S = 2: leave the orders in LDS and learn whether any run has changed in
+    // this half-step (a run at its fixed point stays there).  The flags of
+    // four half-steps rotate: one is cleared two half-steps before it is used.
+    auto publish = [&](int side, uint32_t w, bool changed) {
+      xw[side * S * 64 + part * 64 + lane] = w;
+      if (changed && lane == 0) sh->changed[half_step & 3] = 1;
+      if (tid == 0) sh->changed[(half_step + 2) & 3] = 0;
+      lds_barrier();
+    };
+    auto any_changed = [&]() -> bool { return lane0(sh->changed[half_step++ & 3]) != 0; };
+    int il[MG][g];
+    auto fetch_out = [&](uint32_t w) {
+#pragma unroll
+      for (int r = 0; r < MG; ++r)
+#pragma unroll
+        for (int m = 0; m < g; ++m) B.jf[r][m] = fetch(olane[r][m], oshift[r][m], opm[r][m], w, 1);
+    };
+    auto fetch_in = [&](uint32_t w) {
+#pragma unroll
+      for (int r = 0; r < MG; ++r)
+#pragma unroll
+        for (int m = 0; m < g; ++m) il[r][m] = fetch(ilane[r][m], ishift[r][m], ipm[r][m], w, 0);
+    };
+    uint32_t dw = pack(del);
+    if constexpr (S == 2) {
+      publish(1, dw, false);
+      ++half_step;
+      fetch_out(dw);
+      if (part == 0 && lane == 0) sh->triple[slot] = 0;   // both wavefronts have read it
+    }
+    bool stale = S == 1;   // jf is older than del
+    for (int sweep = 0; sweep < P.i_aa; ++sweep) {
+      bool changed = false;
+      if constexpr (S == 1) {
+        fetch_out(dw);
+        stale = false;
+      }
+#pragma unroll
+      for (int r = 0; r < MG; ++r) {
+        int32_t h[g][g];
+#pragma unroll
+        for (int m = 0; m < g; ++m)
 #pragma unroll
           for (int il = 0; il < g; ++il) {
-            lj[il] = lastj[a * g + il];
-            lv[il] = lastv[a * g + il];
-          }
-          const size_t base = (size_t)c * N;
-          outT[base + a * g + op] = (uint16_t)t;
-          inT[base + d * g + mi] = (uint16_t)t;
-          ocls[base + a * g + op] = (uint8_t)cl;
-          ipos[base + a * g + op] = (int8_t)(d == a ? mi : -1);
-          const int64_t cap = cl == 0 ? cap_c0 : cl == 1 ? cap_c1 : cl == 2 ? cap_c2 : cap_c3;
-          int32_t* h = hp + (base + t) * kRow;
-          uint32_t* rw = raw + (base + t) * kRow;
-          uint64_t kt = 0;
+            if constexpr (kHold) {
+              int32_t row[g];
 #pragma unroll
-          for (int il = 0; il < g; ++il)
-#pragma unroll
-            for (int jl = 0; jl < g; ++jl) {
-              const int i = a * g + il, j = d * g + jl;
-              const int64_t dv = lj[il] == j ? lv[il] : gv[il][jl];
-              // min(D^rem, cap) < 2^31 bytes, a multiple of the unit: exact quotient
-              const uint32_t vb = (uint32_t)(dv < cap ? dv : cap);
-              int32_t v = (int32_t)((vb >> P.unit_shift) * (uint32_t)P.odd_inv);
-              uint32_t rv = (uint32_t)(dv < (int64_t)kRawSaturated ? dv : (int64_t)kRawSaturated);
-              const uint64_t key = ((uint64_t)(uint32_t)v << 24) | (uint64_t)(0xFFFFFF - (t * g2 + il * g + jl));
-              if (i == j) {
-                v = kForbiddenU;
-                rv = kForbidden;
-              } else if (v > 0 && key > kt) {
-                kt = key;
-              }
-              h[il * g + jl] = v;
-              rw[il * g + jl] = rv;
-            }
-          iid[base + t] = (uint8_t)(idv >> 12);
-          if (N % 64 == 0) {   // one family per wavefront
-            kt = wave_max_u(kt);
-            if (lane == 0 && kt) atomicMax((unsigned long long*)&topkey[c], (unsigned long long)kt);
-          } else if (kt) {
-            atomicMax((unsigned long long*)&topkey[c], (unsigned long long)kt);
-          }
-          c += g_dc;
-          t += g_dt;
-          if (t >= N) {
-            t -= N;
-            ++c;
-          }
-        }
-        VP_STAMP(9);
-        // the shuffled starts' permutations (Fisher-Yates on SplitMix64
-        // streams keyed by seed, iteration, family, start, group and side):
-        // one (family, start) pair and 64 of its groups per wavefront, on the
-        // wavefronts the gather leaves idle (on all of them when it leaves
-        // none).  The pair's key prefix is uniform over the wavefront and a
-        // group's two sides share their key, so a lane draws one group.
-        {
-          const int pairs = nc * (NS - 1), gb = (L.G + 63) >> 6;
-          const int busy = (nc * N + 63) >> 6;
-          const int w0 = busy < kWaves ? busy : 0, nw = kWaves - w0;
-          for (int blk = lane0(wave) - w0; blk >= 0 && blk < pairs * gb; blk += nw) {
-            const int cs = blk / gb, a = (blk - cs * gb) * 64 + lane;
-            const int cc = cs / (NS - 1), st = 1 + (cs - cc * (NS - 1));
-            uint64_t k3 = P.seed;
-            k3 = sm_mix(k3 + kGolden) ^ (uint64_t)K;
-            k3 = sm_mix(k3 + kGolden) ^ (uint64_t)(cb + cc);
-            k3 = sm_mix(k3 + kGolden) ^ (uint64_t)st;
-            if (a < L.G) {
-              const uint64_t k5 = sm_mix((sm_mix(k3 + kGolden) ^ (uint64_t)a) + kGolden);
-              int packed = 0;
-#pragma unroll
-              for (int side = 0; side < 2; ++side) {
-                uint64_t state = k5 ^ (uint64_t)side;
-                int perm[g];
-#pragma unroll
-                for (int m = 0; m < g; ++m) perm[m] = m;
-#pragma unroll
-                for (int m = g - 1; m >= 1; --m) {
-                  state += kGolden;
-                  const int j = (int)(sm_mix(state) % (uint64_t)(m + 1));
-                  const int x2 = perm[m];
-                  perm[m] = perm[j];
-                  perm[j] = x2;
-                }
-#pragma unroll
-                for (int m = 0; m < g; ++m) packed |= perm[m] << (2 * m + 8 * side);
-              }
-              // byte 2a + side of the pair's entry (little-endian halfword)
-              *(uint16_t*)(rp + ((size_t)(cc * NS + st) * L.G + a) * 2) = (uint16_t)packed;
+              for (int jj = 0; jj < g; ++jj) row[jj] = hs[r][m][il * g + jj];
+              h[m][il] = pick(row, B.jf[r][m]);
+            } else {
+              h[m][il] = out_credit(r, m, il, B.member(r, m));
             }
           }
-        }
-        VP_STAMP(10);
+        changed |= B.sig[r].improve(h);
       }
-      lds_barrier();
-      VP_STAMP(4);
-      for (int pi = wave; pi < nc * NS; pi += kWaves) {
-        const int c = pi / NS, s = pi - c * NS;
-        FamCtx fc{outT + (size_t)c * N, inT + (size_t)c * N, ipos + (size_t)c * N, ocls + (size_t)c * N,
-                  hp + (size_t)c * N * kRow, cb + c};
-        run_pair<g, MG>(P, fc, sl + (size_t)pi * N, dl + (size_t)pi * N, s, rp + (size_t)pi * L.G * 2, lane,
-                        topkey[c], fe - fb > 1, &pr[pi]);
+      changed = __any(changed);
+      if constexpr (S == 1) {
+        if (sweep > 0 && !changed) break;
+        fetch_in(pack(B.sig));
+      } else {
+        const uint32_t sw = pack(B.sig);
+        publish(0, sw, changed);
+        fetch_in(sw);
+        if (!any_changed() && sweep > 0) break;
       }
-      VP_STAMP(5);
-      // full barrier: the previous iteration's D^rem stores are complete
-      // before the next gather reads D^rem
-      __syncthreads();
-      VP_STAMP(6);
-      // Evaluate (Eq. (9)-(10)): best start per family, best family overall.
-      // Only the wavefronts that write the winner (threads t < N) evaluate.
-      if (wave == 1)
-        for (int x = lane; x < P.FC; x += 64) topkey[x] = 0;   // for the next gather
-      if (wave * 64 < N && fe - fb == 1) {
-        // a one-family shape: its best start wins, no utility to compare
-        // (every lane reads the same scores)
-        int s0 = 0;
-        int64_t F0 = -1;
-        best_start(pr, NS, s0, F0);
-        best_valid = true;
-        VP_STAMP(11);
-        best_S = F0 * P.unit;
-        best_f = cb;
-        best_c = 0;
-        best_s = s0;
-        best_chunk = cb;
-      } else if (wave * 64 < N) {
-        int64_t S = 0, xm = 0, bm = 1;
-        int c = -1, bs = 0;
-        for (int cc = lane; cc < nc; cc += 64) {
-          int s0 = 0;
-          int64_t F0 = -1;
-          best_start(pr + cc * NS, NS, s0, F0);
-          const PairRes& r = pr[cc * NS + s0];
-          int64_t xm2 = 0, bm2 = 1;
-          for (int cl = 0; cl < 2; ++cl) {
-            const int64_t b = L.bw_cls[cl ? VP_PATH_NIC : VP_PATH_PIX];
-            if (r.xmax[cl] * bm2 > xm2 * b) {
-              xm2 = r.xmax[cl];
-              bm2 = b;
+      changed = false;
+#pragma unroll
+      for (int r = 0; r < MG; ++r) {
+        int32_t h[g][g];
+#pragma unroll
+        for (int m = 0; m < g; ++m)
+#pragma unroll
+          for (int jl = 0; jl < g; ++jl) {
+            if constexpr (kHold) {
+              int32_t col[g];
+#pragma unroll
+              for (int ii = 0; ii < g; ++ii) col[ii] = hd[r][m][ii * g + jl];
+              h[m][jl] = pick(col, il[r][m]);
+            } else {
+              h[m][jl] = in_credit(r, m, g == 2 ? il[r][m] & 1 : il[r][m], jl);
             }
           }
-          // Eq. (10) in bytes: served volume and slowest lane
-          const int64_t Sb = r.F * P.unit;
-          xm2 *= P.unit;
-          if (c < 0 || utility_greater(Sb, xm2, bm2, S, xm, bm, P.lambda)) {
-            S = Sb;
-            xm = xm2;
-            bm = bm2;
-            c = cc;
-            bs = s0;
-          }
-        }
-        // wave argmax under the exact order, ties to the lower family index
-        for (int off = nc > 1 ? 32 : 0; off > 0; off >>= 1) {
-          const int64_t S2 = __shfl_xor(S, off), xm2 = __shfl_xor(xm, off), bm2 = __shfl_xor(bm, off);
-          const int c2 = __shfl_xor(c, off), bs2 = __shfl_xor(bs, off);
-          bool take = false;
-          if (c2 >= 0) {
-            if (c < 0) take = true;
-            else if (utility_greater(S2, xm2, bm2, S, xm, bm, P.lambda)) take = true;
-            else if (!utility_greater(S, xm, bm, S2, xm2, bm2, P.lambda) && c2 < c) take = true;
-          }
-          if (take) {
-            S = S2;
-            xm = xm2;
-            bm = bm2;
-            c = c2;
-            bs = bs2;
-          }
-        }
-        // lane 0 holds the chunk's winner (every lane does after the
-        // reduction above): make it uniform
-        S = lane0(S);
-        xm = lane0(xm);
-        bm = lane0(bm);
-        c = lane0(c);
-        bs = lane0(bs);
-        if (!best_valid || utility_greater(S, xm, bm, best_S, best_xm, best_bm, P.lambda)) {
-          best_valid = true;
-          best_S = S;
-          best_xm = xm;
-          best_bm = bm;
-          best_f = cb + c;
-          best_c = c;
-          best_s = bs;
-          best_chunk = cb;
-        }
+        changed |= del[r].improve(h);
       }
-      if (cb + P.FC < fe) {
-        // a later chunk reuses this LDS (and the top keys just cleared): keep
-        // the winner's binding and volumes, and wait for every wavefront
-        if (best_chunk == cb) {
-          const int pi = best_c * NS + best_s;
-          const int32_t* H = hp + (size_t)best_c * N * kRow;
-          const uint32_t* RW = raw + (size_t)best_c * N * kRow;
-          for (int t = tid; t < N; t += kPlanThreads) {
-            const uint8_t s_ = sl[(size_t)pi * N + t], d_ = dl[(size_t)pi * N + t];
-            bsl[t] = s_;
-            bdl[t] = d_;
-            bid[t] = iid[(size_t)best_c * N + t];
-            const int32_t hx = H[t * kRow + s_ * g + d_];
-            bx[t] = (uint32_t)(hx > 0 ? hx : 0);
-            brw[t] = RW[t * kRow + s_ * g + d_];
-          }
-        }
-        __syncthreads();
+      changed = __any(changed);
+      if constexpr (S == 1) {
+        if (!changed) break;
+        dw = pack(del);
+        stale = true;
+      } else {
+        dw = pack(del);
+        publish(1, dw, changed);
+        fetch_out(dw);
+        if (!any_changed()) break;
       }
     }
-
-    VP_STAMP(7);
-    // Step 4: append E* and subtract X(E*) from D^rem and the aggregates.
-    {
-      const int f = best_f, k = kstar;
-      const int lf = f - fbase;
-      const bool live = best_chunk == last_cb;
-      const int pi = best_c * NS + best_s;
-      const uint8_t* SLp = live ? sl + (size_t)pi * N : bsl;
-      const uint8_t* DLp = live ? dl + (size_t)pi * N : bdl;
-      const int32_t* H = hp + (size_t)best_c * N * kRow;
-      const uint32_t* RW = raw + (size_t)best_c * N * kRow;
-      for (int t = tid; t < N; t += kPlanThreads) {
-        const int n = (int)__umulhi((unsigned)t, P.qg_magic), idx = t - n * QG;   // t / QG
-        const uint32_t w = finfo[lf * QG + idx];
-        const int cl = d_cls(w), ss = d_ss(w), ds = d_ds(w);
-        int dn = n;
-        if (cl == VP_PATH_NIC && k) {
-          dn = n + k;
-          if (dn >= nn) dn -= nn;
-        }
-        const int s_ = SLp[t], d_ = DLp[t];
-        const int i = (n * Q + ss) * g + s_, j = (dn * Q + ds) * g + d_;
-        int32_t xu = live ? H[t * kRow + s_ * g + d_] : (int32_t)bx[t];   // units
-        xu = xu > 0 ? xu : 0;   // a self pair serves nothing
-        // the unit is below 2^31 (a cap of at least one unit fits 31 bits)
-        const int64_t x = (int64_t)((uint64_t)(uint32_t)xu * (uint32_t)P.unit);
-        const uint32_t rv = live ? RW[t * kRow + s_ * g + d_] : brw[t];
-        VP_STAMP(12);
-        const uint32_t o = (uint32_t)(K * N + i);
-        at32(gdst, o) = j;
-        at32(ginst, o) = live ? iid[(size_t)best_c * N + t] : bid[t];
-        at32(gbytes, o) = x;
-        if (grecv_src) at32(grecv_src, (uint32_t)(K * N + j)) = i;   // pi_k is a permutation
-        // A residual that did not fit its 32-bit copy is reloaded from
-        // D^rem.  Every use of such a reload stays inside its own branch,
-        // whose stores are relaxed atomic ones so that they are not merged
-        // with the common path's: a use after the branches would make the
-        // common path wait for every store issued so far (the wait counter
-        // covers stores as well).
-        const bool sat = rv >= kRawSaturated;
-        if (gsend_off) {
-          // Sec. 5 buffer layout: where this lane's slice sits in rank i's
-          // send buffer and in its stream to j (bytes sent there before:
-          // D[i][j] minus the residual before this step; D[i][j] is added by
-          // stream_off_kernel after the plan, which keeps its load off this
-          // loop's critical path)
-          at32(gsend_off, o) = sacc[i];
-          if (__builtin_expect(!sat, 1))
-            at32(gstream_off, o) = -(int64_t)rv;
-          else
-            __hip_atomic_store(&at32(gstream_off, o), -at32(gDrem, (uint32_t)(i * N + j)), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-          sacc[i] += x;
-        }
-        VP_STAMP(13);
-        if (xu > 0) {
-          int64_t* dp = &at32(gDrem, (uint32_t)(i * N + j));
-          if (__builtin_expect(!sat, 1)) {
-            const int64_t nv = (int64_t)rv - x;
-            *dp = nv;
-            lastv[i] = nv;
-          } else {
-            const int64_t nv = *dp - x;
-            __hip_atomic_store(dp, nv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&lastv[i], nv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    VP_STAMP(6);
+    if (stale) fetch_out(dw);
+    uint32_t F = 0;
+    xp = xn = 0;
+#pragma unroll
+    for (int r = 0; r < MG; ++r)
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        int32_t x;
+        if constexpr (kHold) {
+          int32_t row[g], col[g];
+#pragma unroll
+          for (int j2 = 0; j2 < g; ++j2) {
+#pragma unroll
+            for (int i2 = 0; i2 < g; ++i2) col[i2] = hs[r][m][i2 * g + j2];
+            if constexpr (g == 2) row[j2] = pick(col, B.sig[r].at_mask(m));
+            else row[j2] = pick(col, B.sig[r].at(m));
           }
-          lastj[i] = j;
-          int kk = dn - n;
-          if (kk < 0) kk += nn;
-          atomicAdd(&agg[(ss * Q + ds) * kS + kk], -xu);
-        }
-      }
-      if (tid == 0) {
-        gfamily[K] = f;
-        if (best_S == 0) {
-          set_err(sh, VP_ERR_NO_PROGRESS);
+          x = pick(row, B.jf[r][m]);
         } else {
-          sh->total_rem -= best_S;
-          sh->K = K + 1;
+          x = out_credit(r, m, B.sig[r].at(m), B.member(r, m));
         }
-        sh->key = 0;
+        const uint32_t xu = (uint32_t)max(x, 0);   // a self pair serves nothing
+        B.xv[r][m] = xu;
+        F += xu;
+        xn = onic[r][m] && xu > xn ? xu : xn;
+        xp = !onic[r][m] && xu > xp ? xu : xp;
       }
-      VP_STAMP(14);
-      // LDS-only barrier: the global stores above need not land before the
-      // next scoring pass (which reads LDS only); the full barrier after it
-      // orders them before the next gather reads D^rem.
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0), other counters untouched
-      __builtin_amdgcn_s_barrier();
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      VP_STAMP(8);
+    F = wave_reduce<OpAdd>(F);
+    if (need_x) {   // the lane maxima only serve comparisons between families
+      xp = wave_reduce<OpMax>(xp);
+      xn = wave_reduce<OpMax>(xn);
     }
+    return F;
+  };
+  // Subtract X(E*) from D^rem and the aggregates and leave the lanes for the
+  // writers.
+  auto apply = [&](const Binding& B, int kstar) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < MG; ++r) {
+      if (!own[r]) continue;
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        const uint32_t e = B.ent[r][m], x = B.xv[r][m];
+        const int il = B.sig[r].at(m), jl = B.member(r, m);
+        out[ga[r] * g + il] = make_uint2((B.dg[r][m] * g + (uint32_t)jl) | (e >> 10) << 16, x);
+        uint32_t* dp = res + ((uint32_t)(ga[r] * G) + B.dg[r][m]) * RW + (uint32_t)(il * g + jl);
+        if constexpr (RL) atomicSub(dp, x);
+        if (x != 0) {
+          if constexpr (RL) {
+          } else if constexpr (kHold) {
+            uint32_t w = 0;
+#pragma unroll
+            for (int t = 0; t < g2; ++t) w = il * g + jl == t ? B.raw[r][m][t] : w;
+            *dp = w - x;
+          } else {
+            *dp -= x;
+          }
+          const int kk = (e & 3) == VP_PATH_NIC ? kstar : 0;
+          atomicSub(&agg[(gq[r] * Q + (int)((e >> 2) & 7)) * kS + kk], (int32_t)x);
+        }
+      }
+    }
+  };
+
+  while (err == 0 && rem != 0) {
+    if (K >= P.k_max) {
+      err = VP_ERR_CAPACITY;
+      break;
+    }
+    VP_STAMP(0);
+    // Step 1: this wavefront's sets, then its patterns.  The A part of the
+    // first pattern does not wait for the sets.
+    int32_t a0[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) a0[m] = *row_of(irow, m);
+    if (kprev != 0 && ns > 0) {
+      // a set's best shift changes only with the column of the last
+      // activation's shift
+      if (P.held) {
+        if (kprev > 0) {
+          const int u0 = kprev - k0;   // an idle lane's sums are not used
+          const int32_t s = shift_sum(kprev);
+#pragma unroll
+          for (int u = 0; u < kHeldShifts; ++u) {
+            if ((u == 2 || u == 4) && u >= SPT) break;   // uniform
+            held[u] = u0 == u ? s : held[u];
+          }
+        }
+        // sums are never negative; a strict gain keeps the lowest of equal shifts
+        int32_t bv = held[0];
+        int bk = k0;
+#pragma unroll
+        for (int u = 1; u < kHeldShifts; ++u) {
+          if ((u == 2 || u == 4) && u >= SPT) break;
+          bk = held[u] > bv ? k0 + u : bk;
+          bv = max(bv, held[u]);
+        }
+        // the lanes of a set are neighbours
+        // and in shift order: of equals the lower lane's stays
+        auto take = [&](int32_t v2, int k2, int o) {
+          bk = v2 + ((lane & o) != 0 ? 1 : 0) > bv ? k2 : bk;
+          bv = max(bv, v2);
+        };
+        if (LPS >= 2) take((int32_t)quad_xor<1>((uint32_t)bv), (int)quad_xor<1>((uint32_t)bk), 1);
+        if (LPS >= 4) take((int32_t)quad_xor<2>((uint32_t)bv), (int)quad_xor<2>((uint32_t)bk), 2);
+        for (int o = 4; o < LPS; o <<= 1) take(__shfl_xor(bv, o), __shfl_xor(bk, o), o);
+        if (has_set && (lane & (LPS - 1)) == 0) rb[my_set] = make_uint2((uint32_t)bv, (uint32_t)bk);
+      } else {
+        // more sets or shifts than the registers hold: every sum again
+        for (int x0 = 0; x0 < ns << P.LPS_log2; x0 += 64) {
+          const int x = x0 + lane;
+          const bool in = x < ns << P.LPS_log2;
+          const int si = sb + (in ? x >> P.LPS_log2 : 0), c0 = 1 + (x & (LPS - 1)) * P.SPT;
+          const int c1 = min(nn, c0 + P.SPT);
+          const uint4 o4 = set_rows[si];
+          int32_t bv = -1;
+          int bk = 0;
+          for (int k = c0; k < c1; ++k) {
+            int32_t s = 0;
+#pragma unroll
+            for (int m = 0; m < 8; ++m) s += row_of(o4, m)[k];
+            if (s > bv) {
+              bv = s;
+              bk = k;
+            }
+          }
+          for (int o = 1; o < LPS; o <<= 1) {
+            const int32_t v2 = __shfl_xor(bv, o);
+            const int k2 = __shfl_xor(bk, o);
+            if (v2 > bv || (v2 == bv && k2 < bk)) {
+              bv = v2;
+              bk = k2;
+            }
+          }
+          if (in && (x & (LPS - 1)) == 0) rb[si] = make_uint2((uint32_t)bv, (uint32_t)bk);
+        }
+      }
+      wave_sync();
+    }
+    VP_STAMP(1);
+    {
+      // candidate of a pattern: {score, shape code, payload}, compared by
+      // score, then by the lower code
+      uint2 r = rb[info0.x >> 16];
+      uint32_t sc = (uint32_t)(a0[0] + a0[1] + a0[2] + a0[3] + a0[4] + a0[5] + a0[6] + a0[7]);
+      if (RW8 > 1)
+        for (int m = 1; m < RW8; ++m) {
+          const uint4 t = rows[min(ib + lane, L.J0 + L.J1 - 1) * RW8 + m];
+#pragma unroll
+          for (int x = 0; x < 8; ++x) sc += (uint32_t)row_of(t, x)[0];
+        }
+      uint32_t code = (r.y << 12) | (info0.x & 0xFFFF), pay = info0.y;
+      sc = ib + lane < ie ? sc + r.x : 0;
+      for (int u = 1; u < nitem; ++u) {
+        const int it = ib + lane + 64 * u, ic = min(it, ie - 1);
+        const uint2 inf = info[ic];
+        r = rb[inf.x >> 16];
+        uint32_t s = r.x;
+        for (int m = 0; m < RW8; ++m) {
+          const uint4 t = rows[ic * RW8 + m];
+#pragma unroll
+          for (int x = 0; x < 8; ++x) s += (uint32_t)row_of(t, x)[0];
+        }
+        const uint32_t c = (r.y << 12) | (inf.x & 0xFFFF);
+        if (it < ie && (s > sc || (s == sc && c < code))) {
+          sc = s;
+          code = c;
+          pay = inf.y;
+        }
+      }
+      // the wavefront's best, or its equals, to the workgroup's argmax
+      if (sc == wave_reduce<OpMax>(sc) && sc != 0)
+        atomicMax((unsigned long long*)&sh->key[K & 1],
+                  (unsigned long long)sc << 33 | (unsigned long long)(0xFFFFF - code) << 13 | pay);
+    }
+    VP_STAMP(2);
+    // in global memory D^rem has to be complete before it is read again
+    if (RL) lds_barrier();
+    else __syncthreads();
+    VP_STAMP(3);
+    const uint64_t key = (uint64_t)lane0((int64_t)sh->key[K & 1]), step_key = (uint64_t)lane0((int64_t)sh->step_key[K & 1]);
+    if (key == 0) {
+      err = VP_ERR_NO_PROGRESS;
+      break;
+    }
+    // the last activation to the schedule, and the next iteration's argmaxes
+    // and shuffle key, on wavefronts that have no run or have ended it
+    Lane ahead;
+    const bool pending = K > written;
+    if (S == 2 && pending && i_first < N) ahead = read_lane_out(i_first, lf_prev);   // its wavefront has a run to do first
+    auto between = [&]() {
+      if (pending && i_first < N) {
+        if (S == 1) ahead = read_lane_out(i_first, lf_prev);
+        write_lane(i_first, K - 1, f_prev, ahead);
+        for (int i = i_first + kPlanThreads; i < N; i += kPlanThreads) write_lane(i, K - 1, f_prev, read_lane_out(i, lf_prev));
+      }
+      written = K;
+      if (wave == kPlanWaves - 1) {
+        const uint64_t k1 = sm_mix((sm_mix(P.seed + kGolden) ^ (uint64_t)(K + 1)) + kGolden);
+        if (lane == 0) {
+          sh->key[(K + 1) & 1] = 0;
+          sh->top[(K + 1) & 1] = 0;
+          sh->step_key[(K + 1) & 1] = k1;
+        }
+      }
+    };
+    const uint32_t code = 0xFFFFF - ((uint32_t)(key >> 13) & 0xFFFFF);
+    const int kstar = (int)(code >> 12), fbase = kstar == 0 ? 0 : (kstar - 1) * L.F1;
+    VP_STAMP(4);
+
+    // Steps 2-4 over the shape's families
+    uint32_t best_F;
+    if ((key & 0x1000) == 0 && NS <= kSlots) {
+      // one family, one start per wavefront: the first start with the highest
+      // score wins, no utility to compare
+      const int lf = (int)(key & 0xFFF);
+      Binding B;
+      uint32_t xp, xn;
+      if constexpr (S == 1) {
+        if (slot < NS) {
+          const uint32_t F = run(B, lf, kstar, fbase, slot, step_key, false, xp, xn);
+          if (lane == 0) atomicMax(&sh->top[K & 1], F << 4 | (uint32_t)(15 - slot));   // F < 2^28
+        }
+      } else {   // a slot without a start repeats the last one: the wavefronts stay in step
+        const uint32_t F = run(B, lf, kstar, fbase, min(slot, NS - 1), step_key, false, xp, xn);
+        if (lane == 0 && slot < NS) prF[slot * S + part] = (int32_t)F;
+      }
+      between();
+      VP_STAMP(7);
+      lds_barrier();
+      VP_STAMP(8);
+      int best;
+      if constexpr (S == 1) {
+        const uint32_t top = (uint32_t)lane0((int32_t)sh->top[K & 1]);
+        best_F = top >> 4;
+        best = 15 - (int)(top & 15);
+      } else {
+        const int2 f2 = ((const int2*)prF)[min(lane & (kSlots - 1), NS - 1)];
+        const uint32_t f = (uint32_t)(f2.x + f2.y);
+        uint32_t m = OpMax::f(f, row_ror<2>(f));   // the four slots repeat along the row
+        m = OpMax::f(m, row_ror<1>(m));
+        best_F = (uint32_t)lane0((int32_t)m);
+        best = __builtin_ctzll(__ballot(f == best_F));
+      }
+      VP_STAMP(9);
+      if (best_F != 0 && slot == best) apply(B, kstar);
+      lf_prev = lf;
+    } else {
+      // FC families at a time, one (family, start) run per slot per round.
+      // A slot that has run another job since the winner's runs
+      // the winner's once more (the same inputs, the same binding).
+      const int ip = kstar ? L.J0 + (int)(code & 0xFFF) : (int)code;
+      const int lb = lane0(cat[L.off_fb + ip]), nf = lane0(cat[L.off_fe + ip]) - lb;
+      bool have = false, redo = false;
+      int64_t best_S = 0, best_xm = 0, best_bm = 1;
+      int best_c = 0, best_s = 0, best_chunk = 0, win_slot = 0;
+      int c0 = 0, nc = min(nf, P.FC), j0 = 0;
+      best_F = 0;
+      between();
+      while (true) {
+        int job = redo ? (best_c - best_chunk) * NS + best_s : j0 + slot;
+        const bool runs = redo ? slot == win_slot : job < nc * NS;
+        if (S == 2) job = min(job, nc * NS - 1);   // the wavefronts stay in step
+        const int cj = job / NS, start = job - cj * NS;
+        Binding B;
+        if (S == 2 || runs) {
+          uint32_t xp, xn;
+          const uint32_t F = run(B, lb + (redo ? best_chunk : c0) + cj, kstar, fbase, start, step_key, true, xp, xn);
+          if (lane == 0 && !redo && runs) {
+            prF[job * S + part] = (int32_t)F;
+            prxp[job * S + part] = (int32_t)xp;
+            prxn[job * S + part] = (int32_t)xn;
+          }
+        }
+        bool held_here = redo;
+        if (!redo) {
+          j0 += kSlots;
+          if (j0 < nc * NS) continue;
+          lds_barrier();
+          // Evaluate (Eq. (9)-(10)): the first start with the highest score
+          // of every family, then the best family
+          const int64_t unit = sh->unit, lambda = sh->lambda;
+          auto score_of = [&](int job) { return S == 1 ? prF[job] : prF[job * S] + prF[job * S + S - 1]; };
+          int64_t V = 0, xm = 0, bm = 1;
+          int c = -1, bs = 0;
+          for (int cc = lane; cc < nc; cc += 64) {
+            int32_t F0 = -1;
+            int s0 = 0;
+            for (int s = 0; s < NS; ++s) {
+              const int32_t f = score_of(cc * NS + s);
+              if (f > F0) {
+                F0 = f;
+                s0 = s;
+              }
+            }
+            int64_t xm2 = 0, bm2 = 1;
+            for (int cl = 0; cl < 2; ++cl) {
+              const int64_t bw = cl ? sh->bw_n : sh->bw_p;
+              const int32_t* px = (cl ? prxn : prxp) + (cc * NS + s0) * S;
+              const int64_t xc = max(px[0], px[S - 1]);
+              if (xc * bm2 > xm2 * bw) {
+                xm2 = xc;
+                bm2 = bw;
+              }
+            }
+            // Eq. (10) in bytes: served volume and slowest lane
+            const int64_t Sb = (int64_t)F0 * unit;
+            xm2 *= unit;
+            if (c < 0 || utility_greater(Sb, xm2, bm2, V, xm, bm, lambda)) {
+              V = Sb;
+              xm = xm2;
+              bm = bm2;
+              c = cc;
+              bs = s0;
+            }
+          }
+          // wave argmax under the exact order, ties to the lower family
+          // index; lanes past the last family hold none
+          for (int off = 1; off < nc; off <<= 1) {
+            const int64_t V2 = __shfl_xor(V, off), xm2 = __shfl_xor(xm, off), bm2 = __shfl_xor(bm, off);
+            const int c2 = __shfl_xor(c, off), bs2 = __shfl_xor(bs, off);
+            bool take = false;
+            if (c2 >= 0) {
+              if (c < 0) take = true;
+              else if (utility_greater(V2, xm2, bm2, V, xm, bm, lambda)) take = true;
+              else if (!utility_greater(V, xm, bm, V2, xm2, bm2, lambda) && c2 < c) take = true;
+            }
+            if (take) {
+              V = V2;
+              xm = xm2;
+              bm = bm2;
+              c = c2;
+              bs = bs2;
+            }
+          }
+          V = lane0(V);
+          xm = lane0(xm);
+          bm = lane0(bm);
+          c = lane0(c);
+          bs = lane0(bs);
+          if (!have || utility_greater(V, xm, bm, best_S, best_xm, best_bm, lambda)) {
+            have = true;
+            best_S = V;
+            best_xm = xm;
+            best_bm = bm;
+            best_c = c0 + c;
+            best_s = bs;
+            best_chunk = c0;
+            best_F = (uint32_t)lane0(score_of(c * NS + bs));
+          }
+          if (c0 + nc < nf) {
+            c0 += nc;
+            nc = min(nf - c0, P.FC);
+            j0 = 0;
+            lds_barrier();   // the next chunk's scores replace these
+            continue;
+          }
+          const int wj = (best_c - best_chunk) * NS + best_s;
+          win_slot = wj & (kSlots - 1);
+          held_here = best_chunk == c0 && wj >= j0 - kSlots;
+        }
+        if (held_here) {
+          if (best_F != 0 && slot == win_slot) apply(B, kstar);
+          break;
+        }
+        redo = true;
+      }
+      lf_prev = lb + best_c;
+    }
+    if (best_F == 0) {
+      err = VP_ERR_NO_PROGRESS;
+      break;
+    }
+    rem -= best_F;
+    kprev = kstar;
+    f_prev = fbase + lf_prev;
+    VP_STAMP(10);
+    lds_barrier();
+    VP_STAMP(11);
+    ++K;
+  }
+  // the last activation; every one before it has been written
+  if (K > written) {
+    if (!RL) __syncthreads();   // D^rem is complete
+    for (int i = i_first; i < N; i += kPlanThreads) write_lane(i, K - 1, f_prev, read_lane_out(i, lf_prev));
   }
 
   if (tid == 0) {
-    P.K[b] = sh->K;
-    if (P.tau) P.tau[b] = sh->err == VP_ERR_INVALID_DEMAND ? 0 : sh->tau;
-    if (sh->err) atomicCAS(P.status + b, 0, sh->err);
-  }
-}
-
-// Stream offsets, completed after the plan: the planner stored minus the
-// pair's residual before each step, and the bytes of the pair sent before it
-// are D[i][j] plus that (Sec. 5 buffer layout).  Block row b of the grid
-// handles matrix b of the batch; its steps k < K[b] only.
-__global__ void __launch_bounds__(256) stream_off_kernel(const int64_t* __restrict__ D, const int32_t* __restrict__ K,
-                                                         const int32_t* __restrict__ dst, int64_t* stream_off, int N,
-                                                         int k_max) {
-  const size_t b = blockIdx.y, NN = (size_t)N * N, KN = (size_t)k_max * N;
-  const int64_t* Db = D + b * NN;
-  const int32_t* db = dst + b * KN;
-  int64_t* sb = stream_off + b * KN;
-  const size_t n = (size_t)K[b] * N;
-  for (size_t x = (size_t)blockIdx.x * 256 + threadIdx.x; x < n; x += (size_t)gridDim.x * 256) {
-    const size_t i = x % (size_t)N;
-    const int j = db[x];   // every lane of a step is written; checked all the same
-    if ((unsigned)j < (unsigned)N) sb[x] += Db[i * N + j];
+    P.K[b] = K;
+    if (P.tau) P.tau[b] = err == VP_ERR_INVALID_DEMAND ? 0 : tau;
+    if (err) atomicCAS(P.status + b, 0, err);
   }
 }
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-template <int g, int MG>
+template <int g, int MG, bool RL, int S>
 vp_status launch_t(const PlanArgs& P, size_t lds, hipStream_t st) {
-  auto kern = plan_kernel<g, MG>;
+  auto kern = plan_kernel<g, MG, RL, S>;
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
       hipSuccess)
     return set_error(VP_ERR_HIP, "cannot raise the planner's LDS limit");
   hipLaunchKernelGGL(kern, dim3((unsigned)P.batch), dim3(kPlanThreads), lds, st, P);
   if (hipGetLastError() != hipSuccess) return set_error(VP_ERR_HIP, "planner launch failed");
-  if (P.stream_off) {
-    const size_t KN = (size_t)P.k_max * P.L.N;
-    const unsigned bx = (unsigned)std::max<size_t>(1, std::min<size_t>((KN + 255) / 256, 2048 / (size_t)P.batch));
-    hipLaunchKernelGGL(stream_off_kernel, dim3(bx, (unsigned)P.batch), dim3(256), 0, st, P.D, P.K, P.dst,
-                       P.stream_off, P.L.N, P.k_max);
-    if (hipGetLastError() != hipSuccess) return set_error(VP_ERR_HIP, "stream offset launch failed");
-  }
   return VP_OK;
 }
 
 template <int g>
-vp_status launch_g(const PlanArgs& P, size_t lds, hipStream_t st, int gpl) {
-  if (gpl <= 1) return launch_t<g, 1>(P, lds, st);
-  if (gpl <= 2) return launch_t<g, 2>(P, lds, st);
-  if (gpl <= 4) return launch_t<g, 4>(P, lds, st);
-  return launch_t<g, 8>(P, lds, st);
+vp_status launch_g(const PlanArgs& P, size_t lds, hipStream_t st, bool res_lds) {
+  const int G = P.L.G;
+  if (G <= 64) return res_lds ? launch_t<g, 1, true, 1>(P, lds, st) : launch_t<g, 1, false, 1>(P, lds, st);
+  if constexpr (g == 2) {
+    if (G <= 128) return res_lds ? launch_t<g, 2, true, 1>(P, lds, st) : launch_t<g, 2, false, 1>(P, lds, st);
+  } else {
+    if (G <= 128) return res_lds ? launch_t<g, 1, true, 2>(P, lds, st) : launch_t<g, 1, false, 2>(P, lds, st);
+  }
+  if (G <= 256) return launch_t<g, 2, false, 2>(P, lds, st);
+  if constexpr (g < 4) return launch_t<g, 4, false, 2>(P, lds, st);
+  return set_error(VP_ERR_UNSUPPORTED, "too many rank groups");
 }
 
 }  // namespace
@@ -1353,16 +1547,15 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   if (QG > kMaxQG || L.Q > 8 || g > 4) return set_error(VP_ERR_UNSUPPORTED, "too many lanes per node");
   if (N > 65535 || L.G > 64 * 8) return set_error(VP_ERR_UNSUPPORTED, "too many ranks for the planner");
   if (L.n_inst > 256) return set_error(VP_ERR_UNSUPPORTED, "too many node-local instances");
-  // the kernel addresses one matrix's schedule and residual with 32-bit byte offsets
+  // the kernel addresses one matrix's schedule with 32-bit byte offsets
   if ((uint64_t)a.p.k_max * (uint64_t)N * 8 >= (uint64_t(1) << 32))
     return set_error(VP_ERR_UNSUPPORTED, "k_max * N too large for the planner");
-  int hmax = 1, mlt = 0, mrt = 0;
+  int hmax = 1, mrt = 0;
   for (int p = 0; p < NP; ++p) {
     hmax = std::max(hmax, c.pat_fe[p] - c.pat_fb[p]);
     int nl = 0;
     for (int v : c.patL[p]) nl += v != 0;
     if (nl > kMaxLTerms) return set_error(VP_ERR_UNSUPPORTED, "too many intra-node lane classes");
-    mlt = std::max(mlt, nl);
     int nr = 0;   // cross-node lanes (a slot pair counts once per lane: several NICs per switch)
     for (int v : c.patR[p]) nr += v;
     if (nr > kMaxRTerms) return set_error(VP_ERR_UNSUPPORTED, "too many NIC lanes in one pattern");
@@ -1391,22 +1584,9 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   P.odd_inv = inv;
   P.odd_lim = ~uint64_t(0) / u;
   P.n_start = NS;
-  P.MLT = mlt;
   P.MRT = mrt;
   P.i_aa = a.p.i_aa;
   P.k_max = a.p.k_max;
-  // shift chunks per NIC-carrying pattern: enough items to occupy every thread
-  // shift scoring: about 8 shifts per lane, lanes per set a power of two
-  {
-    const int shifts = std::max(1, L.nn - 1);
-    int lps = 1;
-    while (lps < 64 && lps * 8 < shifts) lps <<= 1;
-    P.LPS = lps;
-    P.SPT = (shifts + lps - 1) / lps;
-    P.qg_magic = (uint32_t)(((uint64_t(1) << 32) + (uint64_t)QG - 1) / (uint64_t)QG);
-    P.LPS_log2 = 0;
-    while ((1 << P.LPS_log2) < lps) ++P.LPS_log2;
-  }
   P.K = a.K;
   P.family = a.family;
   P.dst = a.dst;
@@ -1418,56 +1598,72 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   P.recv_src = a.recv_src;
   P.status = a.status;
   P.batch = a.batch;
+  // Lanes per NIC-lane set (a power of two) and shifts per lane: up to four
+  // lanes, a quad, combine by two cheap steps, so the shifts of a set go to a
+  // quad where the wavefront has room (two, four or eight shifts per lane),
+  // to more lanes only beyond eight shifts each.  Sets that then do not fit
+  // a wavefront's 64 lanes are summed again in every iteration.
+  {
+    const int shifts = std::max(1, L.nn - 1), sets = std::max(1, L.max_sets);
+    int lg = 0;
+    while (lg < 6 && (kHeldShifts << lg) < shifts) ++lg;
+    while (lg < 2 && (2 << lg) * sets <= 64 && (2 << lg) <= shifts) ++lg;
+    P.LPS_log2 = lg;
+    int spt = (shifts + (1 << lg) - 1) >> lg;
+    P.held = (sets << lg) <= 64 && spt <= kHeldShifts;
+    P.SPT = spt;
+  }
 
-  // the per-rank arrays at the instantiation's fixed offsets first
-  const int gpl = (L.G + 63) / 64;
-  const int MG = gpl <= 1 ? 1 : gpl <= 2 ? 2 : gpl <= 4 ? 4 : 8;
-  size_t o = fixed_lds((size_t)64 * MG * g).end;
-  auto take = [&](int32_t* field, size_t bytes) {
-    *field = (int32_t)o;
-    o = align_up(o + bytes, 16);
-  };
-  take(&P.o_agg, (size_t)((L.nn + 3) | 1) * (L.Q * L.Q + 1) * 4);
-  take(&P.o_terms, (size_t)NP * ((L.TS + 7) & ~7) * 2);
-  take(&P.o_pfb, (size_t)NP * 8);
-  take(&P.o_finfo, (size_t)FL * QG * 2);
-  take(&P.o_rset, (size_t)L.nS * kMaxRTerms * 2);
-  take(&P.o_psid, (size_t)L.J1 * 2);
-  take(&P.o_rbest, (size_t)L.nS * 8);
-  take(&P.o_pbase, (size_t)NP * 4);
-  const size_t fixed = o;
-  const size_t per_fam = align_up((size_t)NS * sizeof(PairRes), 16) + 2 * align_up((size_t)N * 2, 16) +
-                         3 * align_up((size_t)N, 16) + 2 * (size_t)N * (g2 | 1) * 4 + 2 * align_up((size_t)NS * N, 16) + 16 +
-                         align_up((size_t)NS * L.G * 2, 16);
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return set_error(VP_ERR_HIP, "hipGetDevice failed");
   int lds_max = 0;
   if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
     return set_error(VP_ERR_HIP, "hipDeviceGetAttribute failed");
   const size_t budget = (size_t)lds_max;
-  if (fixed + per_fam > budget) return set_error(VP_ERR_UNSUPPORTED, "plan state does not fit in LDS");
-  int FC = (int)std::min<size_t>((size_t)std::min(hmax, 64), (budget - fixed) / per_fam);
-  FC = std::max(FC, 1);
-  P.FC = FC;
-  take(&P.o_pair, (size_t)FC * NS * sizeof(PairRes));
-  take(&P.o_outT, (size_t)FC * N * 2);
-  take(&P.o_inT, (size_t)FC * N * 2);
-  take(&P.o_ipos, (size_t)FC * N);
-  take(&P.o_ocls, (size_t)FC * N);
-  take(&P.o_iid, (size_t)FC * N);
-  take(&P.o_hp, std::max((size_t)FC * N * (g2 | 1) * 4, (size_t)N * 8));   // also the prologue's column sums
-  take(&P.o_raw, (size_t)FC * N * (g2 | 1) * 4);
-  take(&P.o_sl, (size_t)FC * NS * N);
-  take(&P.o_dl, (size_t)FC * NS * N);
-  take(&P.o_top, (size_t)FC * 8);
-  take(&P.o_rp, (size_t)FC * NS * L.G * 2);
+  // Catalogs the planner takes: the library's stated limit, the tables and
+  // one family's whole working set (lists, credits, residuals and every
+  // start's bindings) within one workgroup's LDS.  This kernel needs less.
+  {
+    const int TS8 = (L.TS + 7) & ~7, mg = L.G <= 64 ? 1 : L.G <= 128 ? 2 : L.G <= 256 ? 4 : 8;
+    const size_t n = (size_t)64 * mg * g;
+    size_t need = align_up(112 + 35 * n, 16);
+    for (size_t x : {(size_t)((L.nn + 3) | 1) * (L.Q * L.Q + 1) * 4, (size_t)NP * TS8 * 2, (size_t)NP * 8,
+                     (size_t)FL * QG * 2, (size_t)L.nS * kMaxRTerms * 2, (size_t)L.J1 * 2, (size_t)L.nS * 8,
+                     (size_t)NP * 4, (size_t)NS * 24, 2 * align_up((size_t)N * 2, 16), 3 * align_up((size_t)N, 16),
+                     2 * (size_t)N * (g2 | 1) * 4, 2 * align_up((size_t)NS * N, 16), (size_t)16,
+                     (size_t)NS * L.G * 2})
+      need += align_up(x, 16);
+    if (need > budget) return set_error(VP_ERR_UNSUPPORTED, "plan state does not fit in LDS");
+  }
+  P.FC = std::min(hmax, kFamChunk);
+  size_t o = align_up(sizeof(Shared), 16);
+  auto take = [&](int32_t* field, size_t bytes) {
+    *field = (int32_t)o;
+    o = align_up(o + bytes, 16);
+  };
+  take(&P.o_agg, (size_t)L.kS * (L.Q * L.Q + 1) * 4);
+  take(&P.o_rb, (size_t)(L.nS + 1) * 8);
+  const int parts = L.G <= (g == 2 ? 128 : 64) ? 1 : 2;   // wavefronts per run
+  take(&P.o_pr, (size_t)P.FC * NS * parts * 12);
+  take(&P.o_xw, parts == 1 ? 0 : (size_t)kPlanWaves * 2 * 64 * 4);
+  take(&P.o_out, (size_t)N * 8);
+  take(&P.o_sacc, (size_t)N * 8);
+  // The residual goes to LDS before the family records: a run reads four or
+  // more blocks of the one per lane and a single record of the other, and a
+  // global residual also has to be waited for after every update.
+  const size_t rw = g == 2 ? 4 : g == 3 ? 12 : 16;
+  const size_t res = (size_t)L.G * L.G * rw * 4;
+  const bool res_lds = L.G <= 128 && align_up(o + L.pl_recs, 16) + res <= budget;
+  P.rec_lds = align_up(o + L.pl_end, 16) + (res_lds ? res : 0) <= budget;
+  take(&P.o_tab, P.rec_lds ? L.pl_end : L.pl_recs);
+  take(&P.o_res, res_lds ? res : 0);
   if (o > budget) return set_error(VP_ERR_UNSUPPORTED, "plan state does not fit in LDS");
 
   hipStream_t st = (hipStream_t)stream;
   switch (g) {
-    case 2: return launch_g<2>(P, o, st, gpl);
-    case 3: return launch_g<3>(P, o, st, gpl);
-    case 4: return launch_g<4>(P, o, st, gpl);
+    case 2: return launch_g<2>(P, o, st, res_lds);
+    case 3: return launch_g<3>(P, o, st, res_lds);
+    case 4: return launch_g<4>(P, o, st, res_lds);
   }
   return set_error(VP_ERR_UNSUPPORTED, "gpus_per_switch must be 2, 3 or 4");
 }

@@ -19,13 +19,8 @@ import sys
 
 import numpy as np
 
-PHASES = ["scoring (wave 0)", "scoring barrier", "argmax", "gather + draws", "AA (wave 0 runs)",
-          "AA barrier", "evaluate", "update", "loop top"]
-# (name, from column, to column) of the points stamped inside the phases
-SUB = [("gather: thread 0's items", 3, 9), ("gather: start draws after them", 9, 10),
-       ("gather: barrier", 10, 4), ("evaluate: best start read", 6, 11), ("evaluate: the rest", 11, 7),
-       ("update: reads (lists, binding, credits)", 7, 12), ("update: schedule and layout stores", 12, 13),
-       ("update: residual, aggregates, totals", 13, 14), ("update: barrier", 14, 8)]
+PHASES = ["scoring: sets", "scoring: patterns", "barrier", "argmax", "binding (records, credits, draws)",
+          "AA half-steps", "binding score", "barrier (other starts)", "evaluate", "update", "barrier", "loop top"]
 
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -74,17 +69,14 @@ def main(configs):
         assert lib.vp_phase_stamps_read(buf) == 0
         T = np.frombuffer(buf, dtype=np.uint64).reshape(4096, 16).astype(np.int64)
         K = int(out["K"].item())
-        A, nxt = T[1:K - 1, :9], T[2:K, 0]
+        A, nxt = T[1:K - 1, :12], T[2:K, 0]
         per_iter = float(np.mean(nxt - A[:, 0]))
         print("C%d %s: N=%d, plan %.1f us (stamped copy), K=%d, %.0f cycles per iteration" % (
             c, w.name, N, e0.elapsed_time(e1) * 1e3, K, per_iter), flush=True)
-        cols = [A[:, i + 1] - A[:, i] for i in range(8)] + [nxt - A[:, 8]]
+        order = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11]
+        cols = [A[:, b] - A[:, a] for a, b in zip(order, order[1:])] + [nxt - A[:, 11]]
         for name, d in zip(PHASES, cols):
-            print("   %-18s %7.0f cycles  %5.1f %%" % (name, np.mean(d), 100 * np.mean(d) / per_iter), flush=True)
-        # points inside the phases (thread 0's view)
-        B = T[1:K - 1]
-        for name, a, b in SUB:
-            print("      %-34s %7.0f cycles" % (name, float(np.mean(B[:, b] - B[:, a]))), flush=True)
+            print("   %-34s %7.0f cycles  %5.1f %%" % (name, np.mean(d), 100 * np.mean(d) / per_iter), flush=True)
 
 
 if __name__ == "__main__":

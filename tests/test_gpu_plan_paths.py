@@ -1,0 +1,108 @@
+"""Every path of the planner's dispatch against the oracle, bit-exact, at the
+sizes where the paths meet: rank groups per lane and wavefronts per start,
+D^rem and the family records in LDS or in global memory, sums of shifts held
+in registers or made again, one round of starts or several (a winner whose
+wavefront has run another job since runs again), shapes of one family and of
+many, patterns in one round of lanes or several."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import vpgen
+
+pytestmark = pytest.mark.gpu
+
+UNIT = 4096
+
+
+@pytest.fixture(scope="module")
+def vp():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2609_34340_amd as vp
+    vp.lib()
+    return vp
+
+
+def sparse_demand(rng, N, per_row, scale):
+    """About per_row destinations of every rank; a quarter of the entries near the lane caps' size."""
+    D = rng.integers(1, scale + 1, (N, N)) * (rng.random((N, N)) < per_row / N)
+    D *= np.where(rng.random((N, N)) < 0.25, 40, 1)
+    np.fill_diagonal(D, 0)
+    return (D * UNIT).astype(np.int64)
+
+
+def check(vp, topo, D, **kw):
+    """The whole schedule of up to 32 ranks; of more, where the oracle takes minutes for the thousands of activations
+    a scattered demand needs, the first 24 (the capacity, which both report as exceeded)."""
+    N = topo.n_ranks
+    kw.setdefault("k_max", 64 * N if N <= 32 else 24)
+    cat = vp.Catalog(topo)
+    cat.upload()
+    p = vp.plan_params(N, UNIT, **kw)
+    out = vp.alloc_schedule(N, p.k_max, layout=True)
+    st = vp.new_status()
+    vp.plan(cat, torch.from_numpy(D).cuda(), p, status=st, out=out)
+    torch.cuda.synchronize()
+    o = oracle.Catalog(topo).plan(D, UNIT, check=False, **kw)
+    print("N=%d K=%d %s" % (N, o["K"], kw), flush=True)
+    assert vp.read_status(st) == o["status"] and o["status"] in (0, vp.CAPACITY)
+    g = vp.schedule_to_host(out)
+    assert g["K"] == o["K"] and g["tau"] == o["tau"]
+    K = g["K"]
+    for key in ("family", "dst", "inst", "bytes"):
+        assert np.array_equal(g[key], o[key][:K]), key
+    # the layout outputs, restated from the schedule
+    sent, to, rows = np.zeros(N, np.int64), np.zeros((N, N), np.int64), np.arange(N)
+    send_off, stream_off, recv_src = (out[k][:K].cpu().numpy() for k in ("send_off", "stream_off", "recv_src"))
+    for k in range(K):
+        assert np.array_equal(send_off[k], sent) and np.array_equal(stream_off[k], to[rows, g["dst"][k]]), k
+        assert np.array_equal(recv_src[k][g["dst"][k]], rows), k
+        sent += g["bytes"][k]
+        to[rows, g["dst"][k]] += g["bytes"][k]
+
+
+# groups per lane, wavefronts per start and where D^rem lies, on both sides of each line (G = rank groups)
+SIZES = [
+    vpgen.Topology(63, 1, 1, 2), vpgen.Topology(64, 1, 1, 2), vpgen.Topology(65, 1, 1, 2),   # G = 63, 64, 65
+    vpgen.Topology(16), vpgen.Topology(17), vpgen.Topology(24), vpgen.Topology(25),          # G = 64 ... 100
+    vpgen.Topology(32), vpgen.Topology(33), vpgen.Topology(65, 2, 2, 2),                     # G = 128, 132, 260
+    vpgen.Topology(21, 1, 3, 3), vpgen.Topology(22, 1, 3, 3), vpgen.Topology(43, 1, 3, 3),   # triples: G = 63, 66, 129
+    vpgen.Topology(32, 1, 2, 4), vpgen.Topology(33, 1, 2, 4), vpgen.Topology(65, 1, 2, 4),   # quads: G = 64, 66, 130
+]
+
+
+@pytest.mark.parametrize("topo", SIZES, ids=lambda t: "x".join(map(str, t.as_tuple()[:4])))
+def test_sizes_of_the_runs(vp, topo):
+    rng = np.random.default_rng(topo.n_ranks)
+    check(vp, topo, sparse_demand(rng, topo.n_ranks, 1.5, 6))
+
+
+# records in LDS and (with cross-socket peer to peer, from some size on) in global memory; several rounds of patterns
+@pytest.mark.parametrize("nodes", [1, 2, 3, 8, 16, 20])
+def test_large_catalogs(vp, nodes):
+    topo = vpgen.Topology(nodes, flags=1)
+    rng = np.random.default_rng(nodes)
+    check(vp, topo, sparse_demand(rng, topo.n_ranks, min(2.0, topo.n_ranks / 2), 20))
+
+
+# shifts of a NIC-lane set: two, four and eight per lane, one to sixteen lanes per set, and too many to hold
+@pytest.mark.parametrize("topo", [vpgen.Topology(n) for n in (2, 3, 4, 5, 9, 10)] +
+                         [vpgen.Topology(n, 1, 2, 2) for n in (6, 33, 34, 64)] +
+                         [vpgen.Topology(n, 1, 1, 2) for n in (66, 120)] + [vpgen.Topology(66, 1, 2, 2)],
+                         ids=lambda t: "x".join(map(str, t.as_tuple()[:4])))
+def test_shift_layouts(vp, topo):
+    rng = np.random.default_rng(1000 + topo.n_ranks)
+    check(vp, topo, sparse_demand(rng, topo.n_ranks, 1.5, 6))
+
+
+# starts: fewer than, as many as and more than the wavefronts; shapes of one family and of many
+@pytest.mark.parametrize("topo", [vpgen.Topology(2), vpgen.Topology(1, 1, 2, 2, 2), vpgen.Topology(3, 1, 2, 2, 3),
+                                  vpgen.Topology(2, 1, 2, 3), vpgen.Topology(33, 2, 2, 2)],
+                         ids=lambda t: "x".join(map(str, t.as_tuple()[:5])))
+@pytest.mark.parametrize("n_start", [1, 3, 4, 5, 8, 9, 16])
+def test_rounds_of_starts(vp, topo, n_start):
+    rng = np.random.default_rng(10 * topo.n_ranks + n_start)
+    N = topo.n_ranks
+    D = sparse_demand(rng, N, 3.0, 12)
+    check(vp, topo, D, n_start=n_start, i_aa=[8, 0, 1, 2][n_start % 4], seed=n_start)
