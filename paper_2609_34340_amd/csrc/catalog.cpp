@@ -765,21 +765,24 @@ void build_device_image(vp_catalog& c) {
   for (int si = 0; si < nS; ++si)
     for (int m = 0; m < kMaxRTerms; ++m)
       set_rows[si * kMaxRTerms + m] = (uint16_t)(m < (int)sets[si].size() ? sets[si][m] * L.kS : zero_row);
-  // Family records.  Out-lane of a slot, in family order: class |
-  // destination slot << 2 | rank among the destination's in-lanes of the same
-  // kind (same node or cross-node) << 5 | in-lanes of the other kind << 7 |
-  // local index << 10.  In-lane, cross-node lanes first: class | source slot
-  // << 2 | position in the source's out-list << 5.
+  // Family records.  Out-lane of a slot, in family order: destination slot |
+  // rank among the destination's in-lanes of the same kind (same node or
+  // cross-node) << 3 | in-lanes of the other kind << 5 | local index << 8 |
+  // NIC << 15.  In-lane, cross-node lanes first: source slot | position in
+  // the source's out-list << 3 | the slot has in-lanes of both kinds << 14 |
+  // NIC << 15.
   for (int f = 0; f < FL; ++f) {
     const bool shifted = f >= c.F0;
     // per slot: out-lanes so far, in-lanes so far and in all, by kind
     int n_out[kMaxSlotsPerNode] = {}, seen[kMaxSlotsPerNode][2] = {}, all[kMaxSlotsPerNode][2] = {};
     for (int id : c.lfam[f]) ++all[c.idst[id]][shifted && c.icls[id] == VP_PATH_NIC];
     for (int x = 0; x < QG; ++x) {
-      const int id = c.lfam[f][x], cls = c.icls[id], src = c.isrc[id], dst = c.idst[id];
-      const int kind = shifted && cls == VP_PATH_NIC, same = seen[dst][kind]++, pos = n_out[src]++;
-      recs[((size_t)f * Q + src) * 2 * g + pos] = (uint16_t)(cls | dst << 2 | same << 5 | all[dst][!kind] << 7 | x << 10);
-      recs[((size_t)f * Q + dst) * 2 * g + g + (kind ? same : all[dst][1] + same)] = (uint16_t)(cls | src << 2 | pos << 5);
+      const int id = c.lfam[f][x], nic = c.icls[id] == VP_PATH_NIC, src = c.isrc[id], dst = c.idst[id];
+      const int kind = shifted && nic, same = seen[dst][kind]++, pos = n_out[src]++;
+      recs[((size_t)f * Q + src) * 2 * g + pos] = 
+          (uint16_t)(dst | same << 3 | all[dst][!kind] << 5 | x << 8 | nic << 15);
+      recs[((size_t)f * Q + dst) * 2 * g + g + (kind ? same : all[dst][1] + same)] = 
+          (uint16_t)(src | pos << 3 | (all[dst][0] > 0 && all[dst][1] > 0) << 14 | nic << 15);
     }
   }
 }

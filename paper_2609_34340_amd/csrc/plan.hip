@@ -40,7 +40,7 @@
 // matrix fits beside the tables (up to 160 ranks or so), in the caller's
 // workspace otherwise.  No host round trip happens between iterations.
 //
-// Measured, per activation: 2.3 us at 8 to 128 ranks and 3.6 us at 256 (16
+// Measured, per activation: 2.15-2.25 us at 8 to 128 ranks and 3.6 us at 256 (16
 // wavefronts, five barriers, the family's lists and credits staged in LDS for
 // the runs, schedule stores by the winner's wavefronts: 4.6-4.9 and 6.3 us).
 // A wavefront alone on its SIMD issues a dependent vector or scalar
@@ -415,7 +415,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
   int32_t* prF = (int32_t*)(smem + P.o_pr);         // [FC * NS][S] score of each (family, start) run of the chunk (S parts),
   int32_t* prxp = prF + npr;                        // its largest lane volume on a PCIe-rate path
   int32_t* prxn = prxp + npr;                       // and on a NIC path (units)
-  uint32_t* xw = (uint32_t*)(smem + P.o_xw) + slot * 2 * S * 64;   // S = 2: [2][S * 64] orders of the in- and out-lanes
+  uint32_t* xw = (uint32_t*)(smem + P.o_xw) + slot * 256;   // S = 2: [2][128] orders of the out- and in-lanes
   uint2* out = (uint2*)(smem + P.o_out);            // [N] last activation: {destination | lane << 16, units} of each rank
   uint32_t* colsum = (uint32_t*)(smem + P.o_out);   // [N], prologue only
   int64_t* sacc = (int64_t*)(smem + P.o_sacc);      // [N] bytes each rank has sent so far
@@ -649,7 +649,8 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     if (sh->send_off) {
       x.d = sh->D[(size_t)i * N + j];
       const int a = i / g, c = j / g;
-      x.left = res[((size_t)a * G + c) * RW + (i - a * g) * g + (j - c * g)];
+      const uint32_t* dp = res + ((size_t)a * G + c) * RW + (i - a * g) * g + (j - c * g);
+      x.left = *dp;
     }
     return x;
   };
@@ -676,23 +677,9 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
 
   // The half-steps of S = 2 so far (see publish).
   int half_step = 0;
-  // One MultiStartAA run: local family lf, one start, on this wavefront.
-  // Leaves the binding in `sig` (source of each out-lane), `jf` (member of
-  // its destination), `ent` (out-lane descriptor), `dg` (destination group)
-  // and `xv` (units); returns the binding score F (Eq. (8)) and, if need_x,
-  // the largest lane volume on PCIe-rate and NIC paths.
-  struct Binding {
-    Order<g> sig[MG];
-    int jf[MG][g];   // for g = 2 a mask, all ones for member 1
-    __device__ int member(int r, int m) const { return g == 2 ? jf[r][m] & 1 : jf[r][m]; }
-    uint32_t ent[MG][g], dg[MG][g];
-    uint32_t xv[MG][g];
-    uint32_t raw[RL ? 1 : HM][g][g2];   // residuals of the out-lanes (D^rem in global memory)
-  };
-  auto run = [&](Binding& B, int lf, int kstar, int fbase, int start, uint64_t step_key, bool need_x, uint32_t& xp,
-                 uint32_t& xn) __attribute__((always_inline)) -> uint32_t {
-    // the records of this lane's groups: g out-lanes, then g in-lanes
-    uint32_t rec[MG][g];
+  // The records of local family lf for this lane's groups: g out-lanes, then
+  // g in-lanes, 16 bits each.
+  auto read_records = [&](uint32_t (&rec)[MG][g], int lf) {
 #pragma unroll
     for (int r = 0; r < MG; ++r) {
       const int at = (lf * Q + gq[r]) * g;
@@ -707,61 +694,199 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         for (int m = 0; m < g; ++m) rec[r][m] = ((const uint32_t*)((const char*)(cat + L.off_plan) + L.pl_recs))[at + m];
       }
     }
-    auto half = [&](int r, int x) { return (rec[r][x >> 1] >> (16 * (x & 1))) & 0xFFFFu; };
+  };
+  // all ones if bit `bit` of e is set
+  auto bit_mask = [](uint32_t e, int bit) { return (int32_t)(e << (31 - bit)) >> 31; };
+  // Positions in an in- or out-list are masks for two ranks per group (all
+  // ones is 1), as the orders are.
+  auto pos_index = [](int p) { return g == 2 ? p & 1 : p; };
+  // Out-lanes under shift kstar: descriptor, destination group, position in
+  // that group's in-list.
+  struct OutLanes {
+    uint32_t e[MG][g], d[MG][g];
+    int pos[MG][g];
+    __device__ int32_t nic(int r, int m) const { return (int32_t)(e[r][m] << 16) >> 31; }   // mask
+  };
+  auto decode_out = [&](OutLanes& o, const uint32_t (&rec)[MG][g], int kstar) {
+#pragma unroll
+    for (int r = 0; r < MG; ++r) {
+      int dn = gn[r] + kstar;
+      dn = (int)min((uint32_t)dn, (uint32_t)(dn - nn));
+      const int dq = dn * Q, nq = ga[r] - gq[r];
+      // cross-node lanes come first in an in-list exactly where their source
+      // node is lower: the lanes of the other kind before this one
+      const int32_t far_after = dn >= kstar ? 0 : -1, near_after = gn[r] >= kstar ? -1 : 0;
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        const uint32_t e = m & 1 ? rec[r][m >> 1] >> 16 : rec[r][m >> 1];   // bits above 15 are not read
+        const int32_t nic = bit_mask(e, 15), after = bit_select(nic, far_after, near_after);
+        o.e[r][m] = e;
+        o.d[r][m] = (uint32_t)bit_select(nic, dq, nq) + (e & 7);
+        o.pos[r][m] = g == 2 ? bit_mask(e, 3) | (bit_mask(e, 5) & after)
+                             : (int)((e >> 3) & 3) + ((int)((e >> 5) & 7) & after);
+      }
+    }
+  };
+  // credit: min(D^rem, cap) (none on a lane past the last group), kForbiddenU
+  // for a self pair
+  auto credit = [&](uint32_t w, uint32_t cap, bool self) {
+    return self ? kForbiddenU : (int32_t)(w < cap ? w : cap);
+  };
+  auto lane_cap = [&](int r, int32_t nic) { return (uint32_t)bit_select(nic, (int32_t)my_cap_n[r], (int32_t)my_cap_p[r]); };
+  // The highest-credit triple, ties to the smallest (lane, i, j): `top` is the
+  // wavefront's largest credit (0: none); on the one lane that holds the
+  // triple, `mine`, its key (lane, i, j), and its fields packed for bind_top.
+  // entry(x) is the lane's x-th credit in (group, out-lane, i, j) order, which
+  // is the order of the lanes: a group's out-lanes are in lane order, groups
+  // in node order.
+  struct Triple {
+    uint32_t top, key, pack;
+    bool mine;
+  };
+  auto find_top = [&](const OutLanes& o, auto entry) {
+    constexpr int kEnt = MG * g * g2, kIdx = kEnt <= 8 ? 3 : kEnt <= 16 ? 4 : 5;
+    uint32_t tv = 0, tw = 0;   // the largest credit and the first entry that has it
+    if constexpr (kEnt <= 32) {
+      // credits stay below 2^27: value and (inverted) index in one word
+      uint32_t key = 0;
+#pragma unroll
+      for (int x = 0; x < kEnt; ++x)
+        key = max(key, (uint32_t)max(entry(x), 0) << kIdx | (uint32_t)((1 << kIdx) - 1 - x));
+      tv = key >> kIdx;
+      tw = (uint32_t)((1 << kIdx) - 1) - (key & ((1 << kIdx) - 1));
+    } else {
+#pragma unroll
+      for (int x = 0; x < kEnt; ++x) {
+        const int32_t v = entry(x);
+        tw = v > (int32_t)tv ? (uint32_t)x : tw;
+        tv = (uint32_t)max((int32_t)tv, v);
+      }
+    }
+    // this lane's fields, while the reduction is under way
+    const uint32_t om = tw / g2, e = tw % g2;
+    uint32_t t = 0, d = 0, a = 0;
+    int mi = 0;
+#pragma unroll
+    for (int r = 0; r < MG; ++r)
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        const bool it = om == (uint32_t)(r * g + m);
+        t = it ? (uint32_t)(gn[r] * QG) + ((o.e[r][m] >> 8) & 31) : t;
+        d = it ? o.d[r][m] : d;
+        mi = it ? pos_index(o.pos[r][m]) : mi;
+        a = it ? (uint32_t)ga[r] : a;
+      }
+    Triple T;
+    T.key = t * (uint32_t)g2 + e;
+    T.pack = a | d << 9 | (om % g) << 18 | (e / g) << 20 | (e % g) << 22 | (uint32_t)mi << 24;
+    T.top = wave_reduce<OpMax>(tv);
+    T.mine = tv == T.top;
+    const uint64_t eq = __ballot(T.mine);
+    if ((eq & (eq - 1)) != 0) {   // the whole wavefront reduces
+      const uint32_t key = T.mine ? T.key : ~0u, lo = wave_reduce<OpMin>(key);
+      T.mine = key == lo;
+    }
+    return T;
+  };
+  // Both sides' shuffled orders of a start: independent Fisher-Yates shuffles
+  // of every group's sources and destinations on SplitMix64 streams keyed by
+  // seed, iteration, family, start, group and side; the key prefix is uniform
+  // over the wavefront.
+  auto draw = [&](Order<g> (&sig)[MG], Order<g> (&del)[MG], uint64_t step_key, int family, int start) {
+    uint64_t k3 = step_key ^ (uint64_t)family;
+    k3 = sm_mix(k3 + kGolden) ^ (uint64_t)start;
+    const uint64_t k4 = sm_mix(k3 + kGolden);
+#pragma unroll
+    for (int r = 0; r < MG; ++r) {
+      const uint64_t k5 = sm_mix((k4 ^ (uint64_t)ga[r]) + kGolden);
+      sig[r].shuffle(k5);
+      del[r].shuffle(k5 ^ 1);
+    }
+  };
+  auto order_word = [&](const Order<g> (&a)[MG]) -> uint32_t {
+    uint32_t w = a[0].word();
+#pragma unroll
+    for (int r = 1; r < MG; ++r) w |= a[r].word() << (r * Order<g>::bits);
+    return w;
+  };
+
+  // One MultiStartAA run: local family lf, one start, on this wavefront.
+  // Leaves the binding in `sig` (source of each out-lane), `jf` (member of
+  // its destination), `ent` (out-lane descriptor), `dg` (destination group)
+  // and `xv` (units); returns the binding score F (Eq. (8)) and, if need_x,
+  // the largest lane volume on PCIe-rate and NIC paths.
+  struct Binding {
+    Order<g> sig[MG];
+    int jf[MG][g];   // for g = 2 a mask, all ones for member 1
+    __device__ int member(int r, int m) const { return g == 2 ? jf[r][m] & 1 : jf[r][m]; }
+    OutLanes o;
+    uint32_t xv[MG][g];
+    uint32_t left[RL ? 1 : MG][g];   // D^rem in global memory: the residual of each lane's pair
+  };
+  auto run = [&](Binding& B, int lf, int kstar, int fbase, int start, uint64_t step_key, bool need_x, uint32_t& xp,
+                 uint32_t& xn) __attribute__((always_inline)) -> uint32_t {
+    uint32_t rec[MG][g];
+    read_records(rec, lf);
+    OutLanes& o = B.o;
+    decode_out(o, rec, kstar);
     uint32_t raw[HM][g][g2], rin[HM][g][g2];
-    // the other side of every lane: its group's word and bit there, and the
-    // position in its list
-    uint32_t olane[MG][g], oshift[MG][g], ilane[MG][g], ishift[MG][g];
-    int opos[MG][g], ipos[MG][g];
-    bool oself[MG][g], iself[MG][g], onic[MG][g];
-    uint32_t ocap[MG][g], icap[MG][g];
-    uint32_t sg[MG][g];
     // where group d's order is: its word (byte offset: lane, and with two
     // wavefronts its part) and the bit its order starts at
-    auto word_of = [&](uint32_t d) { return S == 1 ? (d & 63) << 2 : (d & 127) << 2; };
-    auto shift_of = [&](uint32_t d) { return (S == 1 ? d >> 6 : d >> 7) * Order<g>::bits; };
+    auto word_of = [&](uint32_t d) {
+      constexpr uint32_t n = 64 * S;
+      return MG == 1 ? d << 2 : (d & (n - 1)) << 2 | (d / n * Order<g>::bits) << 16;
+    };
+    uint32_t oword[MG][g], iword[MG][g];   // word | bit << 16
+    int ipos[MG][g];
+    bool oself[MG][g], iself[MG][g];
+    uint32_t ocap[MG][g], icap[MG][g], sg[MG][g];
 #pragma unroll
     for (int r = 0; r < MG; ++r) {
 #pragma unroll
-      for (int m = 0; m < g; ++m) {
-        const uint32_t e = half(r, m);
-        B.ent[r][m] = e;
-        onic[r][m] = (e & 3) == VP_PATH_NIC;
-        const int kk = onic[r][m] ? kstar : 0;
-        int dn = gn[r] + kk;
-        dn = (int)min((uint32_t)dn, (uint32_t)(dn - nn));
-        const uint32_t d = (uint32_t)(dn * Q) + ((e >> 2) & 7);
-        // rank of the lane inside the in-list of group d: cross-node lanes
-        // come first exactly where their source node is lower
-        opos[r][m] = (int)((e >> 5) & 3) + ((kk != 0) != (dn >= kstar) ? (int)((e >> 7) & 7) : 0);
-        B.dg[r][m] = d;
-        oself[r][m] = own[r] && d == (uint32_t)ga[r];
-        ocap[r][m] = onic[r][m] ? my_cap_n[r] : my_cap_p[r];
-        olane[r][m] = word_of(d);
-        oshift[r][m] = shift_of(d);
-        if constexpr (kHold) load_block<g>(res + ((uint32_t)(ga[r] * G) + d) * RW, raw[r][m]);
+      for (int m = 0; m < g; ++m)
+        if constexpr (kHold) load_block<g>(res + ((uint32_t)(ga[r] * G) + o.d[r][m]) * RW, raw[r][m]);
+      // in-lanes, stored cross-node lanes first: same-node lanes lead where
+      // the source node of the others is the higher one
+      int sn = gn[r] - kstar;
+      sn = (int)min((uint32_t)sn, (uint32_t)(sn + nn));
+      const int sq = sn * Q, nq = ga[r] - gq[r];
+      uint32_t ein[g];
+      if constexpr (g == 2) {
+        const uint32_t w = rec[r][1];
+        const int32_t turn = bit_mask(w, 14) & (gn[r] >= kstar ? 0 : 16);   // one lane of each kind
+        const uint32_t v = __builtin_amdgcn_alignbit(w, w, (uint32_t)turn);
+        ein[0] = v;
+        ein[1] = v >> 16;
+      } else {
+        auto in_at = [&](int x) { return (x & 1 ? rec[r][x >> 1] >> 16 : rec[r][x >> 1]) & 0xFFFFu; };
+        int nr = 0;
+#pragma unroll
+        for (int m = 0; m < g; ++m) nr += (int)(in_at(g + m) >> 15);
+        const int rot = gn[r] >= kstar ? 0 : nr;
+#pragma unroll
+        for (int m = 0; m < g; ++m) {
+          ein[m] = in_at(g + m);
+#pragma unroll
+          for (int t = 1; t < g; ++t) ein[m] = (uint32_t)bit_select(rot == t ? -1 : 0, (int)in_at(g + (m + t) % g), (int)ein[m]);
+        }
       }
-      // in-lanes, stored cross-node lanes first
-      int nr = 0;
-#pragma unroll
-      for (int m = 0; m < g; ++m) nr += (half(r, g + m) & 3) == VP_PATH_NIC;
-      const int rot = gn[r] >= kstar ? 0 : nr;
 #pragma unroll
       for (int m = 0; m < g; ++m) {
-        uint32_t e = half(r, g + m);
-#pragma unroll
-        for (int t = 1; t < g; ++t) e = rot == t ? half(r, g + (m + t) % g) : e;
-        const bool nic = (e & 3) == VP_PATH_NIC;
-        int sn = gn[r] - (nic ? kstar : 0);
-        sn = (int)min((uint32_t)sn, (uint32_t)(sn + nn));
-        const uint32_t s = (uint32_t)(sn * Q) + ((e >> 2) & 7);
+        const uint32_t e = ein[m];
+        const int32_t nic = bit_mask(e, 15);
+        const uint32_t s = (uint32_t)bit_select(nic, sq, nq) + (e & 7);
         sg[r][m] = s;
-        iself[r][m] = own[r] && s == (uint32_t)ga[r];
-        icap[r][m] = nic ? my_cap_n[r] : my_cap_p[r];
-        ipos[r][m] = (int)((e >> 5) & 3);
-        ilane[r][m] = word_of(s);
-        ishift[r][m] = shift_of(s);
         if constexpr (kHold) load_block<g>(res + (s * (uint32_t)G + (uint32_t)ga[r]) * RW, rin[r][m]);
+        iself[r][m] = own[r] && s == (uint32_t)ga[r];
+        icap[r][m] = lane_cap(r, nic);
+        ipos[r][m] = g == 2 ? bit_mask(e, 3) : (int)((e >> 3) & 3);
+        iword[r][m] = word_of(s);
+      }
+#pragma unroll
+      for (int m = 0; m < g; ++m) {
+        oself[r][m] = own[r] && o.d[r][m] == (uint32_t)ga[r];
+        ocap[r][m] = lane_cap(r, o.nic(r, m));
+        oword[r][m] = word_of(o.d[r][m]);
       }
     }
     Order<g> del[MG];
@@ -772,25 +897,9 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         del[r].identity();
       }
     } else {
-      // independent Fisher-Yates shuffles of every group's sources and
-      // destinations on SplitMix64 streams keyed by seed, iteration, family,
-      // start, group and side; the key prefix is uniform over the wavefront
-      uint64_t k3 = step_key ^ (uint64_t)(fbase + lf);
-      k3 = sm_mix(k3 + kGolden) ^ (uint64_t)start;
-      const uint64_t k4 = sm_mix(k3 + kGolden);
-#pragma unroll
-      for (int r = 0; r < MG; ++r) {
-        const uint64_t k5 = sm_mix((k4 ^ (uint64_t)ga[r]) + kGolden);
-        B.sig[r].shuffle(k5);
-        del[r].shuffle(k5 ^ 1);
-      }
+      draw(B.sig, del, step_key, fbase + lf, start);
     }
-    // credits: min(D^rem, cap), kForbiddenU for a self pair
     int32_t hs[HM][g][g2], hd[HM][g][g2];
-    // (none at all on a lane past the last group)
-    auto credit = [&](uint32_t w, uint32_t cap, bool self) {
-      return self ? kForbiddenU : (int32_t)(w < cap ? w : cap);
-    };
     if constexpr (kHold) {
 #pragma unroll
       for (int r = 0; r < MG; ++r)
@@ -800,118 +909,73 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
           for (int e = 0; e < g2; ++e) {
             hs[r][m][e] = credit(raw[r][m][e], ocap[r][m], e / g == e % g && oself[r][m]);
             hd[r][m][e] = credit(rin[r][m][e], icap[r][m], e / g == e % g && iself[r][m]);
-            if constexpr (!RL) B.raw[r][m][e] = raw[r][m][e];
           }
     }
     // credit of out-lane (r, m) from source il to member jl, and of in-lane
     // (r, m) from member il to destination jl
     auto out_credit = [&](int r, int m, int il, int jl) {
-      return credit(res[((uint32_t)(ga[r] * G) + B.dg[r][m]) * RW + il * g + jl], ocap[r][m], il == jl && oself[r][m]);
+      return credit(res[((uint32_t)(ga[r] * G) + o.d[r][m]) * RW + il * g + jl], ocap[r][m], il == jl && oself[r][m]);
     };
     auto in_credit = [&](int r, int m, int il, int jl) {
       return credit(res[(sg[r][m] * (uint32_t)G + (uint32_t)ga[r]) * RW + il * g + jl], icap[r][m], il == jl && iself[r][m]);
     };
-    int prot_o[MG], prot_i[MG];   // the protected lane's out- and in-list position, -1 elsewhere
+    // Start 0: the canonical binding with the highest-credit triple put in;
+    // its lane's out- and in-list positions are protected (-1: none here).
+    int prot_o[MG], prot_i[MG];
 #pragma unroll
     for (int r = 0; r < MG; ++r) prot_o[r] = prot_i[r] = -1;
-    // canonical binding plus the highest-credit triple, ties to the smallest
-    // (lane, i, j): out-lanes of a group are in lane order
-    auto bind_top = [&](bool mine, int r0, int m0, int il, int jl, int d, int mi) {
+    auto bind_top = [&](int a, int m0, int il, int jl, int d, int mi) {
 #pragma unroll
       for (int r = 0; r < MG; ++r) {
         // members are still in order: the one to move is at its own position
-        const bool so = mine && r == r0, di = ga[r] == d && own[r];
+        const bool so = ga[r] == a && own[r], di = ga[r] == d && own[r];
         prot_o[r] = so ? m0 : -1;
         B.sig[r].swap_if(so, m0, il);
         prot_i[r] = di ? mi : -1;
         del[r].swap_if(di, mi, jl);
       }
     };
-    if (start == 0) {
-      constexpr int kEnt = MG * g * g2, kIdx = kEnt <= 2 ? 1 : kEnt <= 8 ? 3 : kEnt <= 16 ? 4 : 5;
-      auto entry = [&](int x) -> int32_t {   // credit x of this lane, in (lane, i, j) order
+    auto bind_pack = [&](uint32_t w) {
+      bind_top((int)(w & 511), (int)((w >> 18) & 3), (int)((w >> 20) & 3), (int)((w >> 22) & 3), (int)((w >> 9) & 511),
+               (int)((w >> 24) & 3));
+    };
+    auto top_here = [&]() {
+      return find_top(o, [&](int x) -> int32_t {
         const int r = x / (g * g2), m = x / g2 % g, e = x % g2;
         if constexpr (kHold) return hs[r][m][e];
         else return out_credit(r, m, e / g, e % g);
-      };
-      uint32_t tv = 0, tw = 0;   // the largest credit and the first entry that has it
-      if constexpr (kEnt <= 32) {
-        // credits stay below 2^27: value and (inverted) index in one word
-        int32_t key = 0;
-#pragma unroll
-        for (int x = 0; x < kEnt; ++x) key = max(key, entry(x) << kIdx | ((1 << kIdx) - 1 - x));
-        static_assert(kIdx <= 4 || kEnt > 16, "index bits");
-        tv = (uint32_t)key >> kIdx;
-        tw = (uint32_t)((1 << kIdx) - 1) - ((uint32_t)key & ((1 << kIdx) - 1));
-      } else {
-#pragma unroll
-        for (int x = 0; x < kEnt; ++x) {
-          const int32_t v = entry(x);
-          tw = v > (int32_t)tv ? (uint32_t)x : tw;
-          tv = (uint32_t)max((int32_t)tv, v);
-        }
+      });
+    };
+    if constexpr (S == 1) {
+      if (start == 0) {
+        const Triple T = top_here();
+        if (T.top != 0) bind_pack(read_lane(T.pack, __builtin_ctzll(__ballot(T.mine))));
       }
-      const uint32_t top = wave_reduce<OpMax>(tv);
-      if (top != 0) {
-        uint64_t eq = __ballot(tv == top);
-        if ((eq & (eq - 1)) != 0) {
-          // the lowest (lane, i, j) among the lanes' first entries
-          uint32_t t = 0;
-#pragma unroll
-          for (int r = 0; r < MG; ++r)
-#pragma unroll
-            for (int m = 0; m < g; ++m)
-              t = tw / g2 == (uint32_t)(r * g + m) ? (uint32_t)(gn[r] * QG) + (B.ent[r][m] >> 10) : t;
-          const uint32_t key = tv == top ? t * (uint32_t)g2 + tw % g2 : ~0u;
-          eq = __ballot(key == wave_reduce<OpMin>(key));
-        }
-        const int tl = __builtin_ctzll(eq);   // the lane, its out-lane and (i, j)
-        const uint32_t w = read_lane(tw, tl);
-        const uint32_t om = w / g2, e = w % g2;
-        const int r0 = (int)(om / g), m0 = (int)(om % g), il = (int)(e / g), jl = (int)(e % g);
-        uint32_t dd = B.dg[0][0];
-        int pp = opos[0][0];
-#pragma unroll
-        for (int r = 0; r < MG; ++r)
-#pragma unroll
-          for (int m = 0; m < g; ++m) {
-            dd = om == (uint32_t)(r * g + m) ? B.dg[r][m] : dd;
-            pp = om == (uint32_t)(r * g + m) ? opos[r][m] : pp;
-          }
-        const int d = (int)read_lane(dd, tl), mi = (int)read_lane((uint32_t)pp, tl);
-        if constexpr (S == 1) {
-          bind_top(lane == tl, r0, m0, il, jl, d, mi);
-        } else {
-          // the two wavefronts' triples meet in one word: credit, (lane, i, j)
-          // inverted (below 2^14), destination group, position there
-          uint32_t t = 0;
-#pragma unroll
-          for (int r = 0; r < MG; ++r)
-#pragma unroll
-            for (int m = 0; m < g; ++m) t = om == (uint32_t)(r * g + m) ? (uint32_t)(gn[r] * QG) + (B.ent[r][m] >> 10) : t;
-          if (lane == tl)
-            atomicMax((unsigned long long*)&sh->triple[slot],
-                      (unsigned long long)top << 32 | (unsigned long long)(0x3FFF - (t * (uint32_t)g2 + e)) << 16 |
-                          (unsigned long long)(d << 2 | mi));
-        }
+    } else {
+      if (start == 0) {
+        // the two wavefronts' triples meet in one word: credit, (lane, i, j)
+        // inverted (below 2^14), destination group, position there
+        const Triple T = top_here();
+        if (T.mine && T.top != 0)
+          atomicMax((unsigned long long*)&sh->triple[slot],
+                    (unsigned long long)T.top << 32 | (unsigned long long)(0x3FFF - T.key) << 16 |
+                        (unsigned long long)(((T.pack >> 9) & 511) << 2 | ((T.pack >> 24) & 3)));
       }
-    }
-    if constexpr (S == 2) {
       lds_barrier();   // every wavefront comes here: runs are in step
       if (start == 0) {
         const uint64_t w = (uint64_t)lane0((int64_t)sh->triple[slot]);
         if (w != 0) {
           const uint32_t key = 0x3FFF - ((uint32_t)(w >> 16) & 0x3FFF), t = key / (uint32_t)g2, e = key % (uint32_t)g2;
-          int r0 = -1, m0 = 0;
+          int a = -1, m0 = 0;   // on the lane that owns it
 #pragma unroll
           for (int r = 0; r < MG; ++r)
 #pragma unroll
             for (int m = 0; m < g; ++m)
-              if (own[r] && (uint32_t)(gn[r] * QG) + (B.ent[r][m] >> 10) == t) {
-                r0 = r;
+              if (own[r] && (uint32_t)(gn[r] * QG) + ((o.e[r][m] >> 8) & 31) == t) {
+                a = ga[r];
                 m0 = m;
               }
-          bind_top(r0 >= 0, r0, m0, (int)(e / g), (int)(e % g), (int)((w >> 2) & 0x3FFF), (int)(w & 3));
+          bind_top(a, m0, (int)(e / g), (int)(e % g), (int)((w >> 2) & 0x3FFF), (int)(w & 3));
         }
       }
     }
@@ -922,7 +986,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     for (int r = 0; r < MG; ++r)
 #pragma unroll
       for (int m = 0; m < g; ++m) {
-        const int mi = opos[r][m];
+        const int mi = pos_index(o.pos[r][m]);
         if (oself[r][m] && B.sig[r].at(m) == del[r].at(mi)) {
           int pi = -1, po = -1;
 #pragma unroll
@@ -940,14 +1004,8 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     // not moved.  Stopping there gives the same binding as stopping after a
     // whole unchanged sweep.
     auto pack = [&](const Order<g> (&a)[MG]) -> uint32_t {
-      if constexpr (g == 2 && MG == 1) {
-        return (uint32_t)a[0].p;
-      } else {
-        uint32_t w = a[0].word();
-#pragma unroll
-        for (int r = 1; r < MG; ++r) w |= a[r].word() << (r * Order<g>::bits);
-        return w;
-      }
+      if constexpr (g == 2 && MG == 1) return (uint32_t)a[0].p;
+      else return order_word(a);
     };
     // entry `i` of a row (or column) of credits, i a member or, for g = 2, its mask
     auto pick = [&](const int32_t (&c)[g], int i) {
@@ -962,10 +1020,11 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     };
     // Member at the other side of a lane, from this lane's view of that side's
     // orders `w`: a permute, or (S = 2) the words that publish() left in LDS.
-    auto fetch = [&](uint32_t from, uint32_t shift, int pos, uint32_t w, int side) {
+    auto fetch = [&](uint32_t from, int pos, uint32_t w, int side) {
+      const uint32_t at = MG == 1 ? from : from & 0xFFFF, shift = MG == 1 ? 0 : from >> 16;
       uint32_t v;
-      if constexpr (S == 1) v = (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)w);
-      else v = *(const uint32_t*)((const char*)(xw + side * S * 64) + from);
+      if constexpr (S == 1) v = (uint32_t)__builtin_amdgcn_ds_bpermute((int)at, (int)w);
+      else v = *(const uint32_t*)((const char*)(xw + side * S * 64) + at);
       if constexpr (g == 2) {   // a mask: all ones is member 1 (`pos` is one as well)
         if constexpr (MG == 1) return (int)v ^ pos;
         else return ((int)(v << (31 - shift)) >> 31) ^ pos;
@@ -974,14 +1033,6 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         return Order<g>::member(v, pos);
       }
     };
-    int opm[MG][g], ipm[MG][g];
-#pragma unroll
-    for (int r = 0; r < MG; ++r)
-#pragma unroll
-      for (int m = 0; m < g; ++m) {
-        opm[r][m] = g == 2 ? -opos[r][m] : opos[r][m];
-        ipm[r][m] = g == 2 ? -ipos[r][m] : ipos[r][m];
-      }
     VP_STAMP(5);
     // S = 2: leave the orders in LDS and learn whether any run has changed in
     // this half-step (a run at its fixed point stays there).  The flags of
@@ -998,13 +1049,13 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
 #pragma unroll
       for (int r = 0; r < MG; ++r)
 #pragma unroll
-        for (int m = 0; m < g; ++m) B.jf[r][m] = fetch(olane[r][m], oshift[r][m], opm[r][m], w, 1);
+        for (int m = 0; m < g; ++m) B.jf[r][m] = fetch(oword[r][m], o.pos[r][m], w, 1);
     };
     auto fetch_in = [&](uint32_t w) {
 #pragma unroll
       for (int r = 0; r < MG; ++r)
 #pragma unroll
-        for (int m = 0; m < g; ++m) il[r][m] = fetch(ilane[r][m], ishift[r][m], ipm[r][m], w, 0);
+        for (int m = 0; m < g; ++m) il[r][m] = fetch(iword[r][m], ipos[r][m], w, 0);
     };
     uint32_t dw = pack(del);
     if constexpr (S == 2) {
@@ -1081,6 +1132,15 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     }
     VP_STAMP(6);
     if (stale) fetch_out(dw);
+    // in global memory the residuals that the winner lowers are asked for
+    // ahead of the comparison of the starts
+    if constexpr (!RL) {
+#pragma unroll
+      for (int r = 0; r < MG; ++r)
+#pragma unroll
+        for (int m = 0; m < g; ++m)
+          B.left[r][m] = res[((uint32_t)(ga[r] * G) + o.d[r][m]) * RW + (uint32_t)(B.sig[r].at(m) * g + B.member(r, m))];
+    }
     uint32_t F = 0;
     xp = xn = 0;
 #pragma unroll
@@ -1104,8 +1164,8 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         const uint32_t xu = (uint32_t)max(x, 0);   // a self pair serves nothing
         B.xv[r][m] = xu;
         F += xu;
-        xn = onic[r][m] && xu > xn ? xu : xn;
-        xp = !onic[r][m] && xu > xp ? xu : xp;
+        xn = max(xn, xu & (uint32_t)o.nic(r, m));
+        xp = max(xp, xu & ~(uint32_t)o.nic(r, m));
       }
     F = wave_reduce<OpAdd>(F);
     if (need_x) {   // the lane maxima only serve comparisons between families
@@ -1122,24 +1182,14 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
       if (!own[r]) continue;
 #pragma unroll
       for (int m = 0; m < g; ++m) {
-        const uint32_t e = B.ent[r][m], x = B.xv[r][m];
+        const uint32_t e = B.o.e[r][m], x = B.xv[r][m], d = B.o.d[r][m];
         const int il = B.sig[r].at(m), jl = B.member(r, m);
-        out[ga[r] * g + il] = make_uint2((B.dg[r][m] * g + (uint32_t)jl) | (e >> 10) << 16, x);
-        uint32_t* dp = res + ((uint32_t)(ga[r] * G) + B.dg[r][m]) * RW + (uint32_t)(il * g + jl);
+        out[ga[r] * g + il] = make_uint2((d * g + (uint32_t)jl) | (e & 0x1F00) << 8, x);
+        uint32_t* dp = res + ((uint32_t)(ga[r] * G) + d) * RW + (uint32_t)(il * g + jl);
         if constexpr (RL) atomicSub(dp, x);
-        if (x != 0) {
-          if constexpr (RL) {
-          } else if constexpr (kHold) {
-            uint32_t w = 0;
-#pragma unroll
-            for (int t = 0; t < g2; ++t) w = il * g + jl == t ? B.raw[r][m][t] : w;
-            *dp = w - x;
-          } else {
-            *dp -= x;
-          }
-          const int kk = (e & 3) == VP_PATH_NIC ? kstar : 0;
-          atomicSub(&agg[(gq[r] * Q + (int)((e >> 2) & 7)) * kS + kk], (int32_t)x);
-        }
+        else if (x != 0) *dp = B.left[r][m] - x;
+        // the lane's node block: its own node's, or the shifted one
+        atomicSub(&agg[gq[r] * Q * kS + (int)(e & 7) * kS + (B.o.nic(r, m) & kstar)], (int32_t)x);
       }
     }
   };
@@ -1645,7 +1695,7 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   take(&P.o_rb, (size_t)(L.nS + 1) * 8);
   const int parts = L.G <= (g == 2 ? 128 : 64) ? 1 : 2;   // wavefronts per run
   take(&P.o_pr, (size_t)P.FC * NS * parts * 12);
-  take(&P.o_xw, parts == 1 ? 0 : (size_t)kPlanWaves * 2 * 64 * 4);
+  take(&P.o_xw, parts == 1 ? 0 : (size_t)kPlanWaves / 2 * 256 * 4);
   take(&P.o_out, (size_t)N * 8);
   take(&P.o_sacc, (size_t)N * 8);
   // The residual goes to LDS before the family records: a run reads four or
