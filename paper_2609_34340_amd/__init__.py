@@ -126,7 +126,7 @@ def _np(a: np.ndarray):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # ctypes converts the address by the argument's type
 
 
 def _dev(t: torch.Tensor, dtype, name: str):
@@ -136,8 +136,11 @@ def _dev(t: torch.Tensor, dtype, name: str):
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    # the raw handle of the current device's current stream, without a Stream object around it: the small calls are
+    # bound by the host (a decode step's demand and control words 19 us a pass, of which the kernels take 9)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def topology(topo) -> _Topology:
@@ -282,9 +285,8 @@ def demand(routing: torch.Tensor, n_ranks: int, n_experts: int, unit: int, first
                    dest_off=torch.empty(n_ranks + 1, dtype=torch.int64, device=dev))
     if status is None:
         status = new_status(dev)
-    wsb = demand_workspace_bytes(R, T, k, n_experts)
     if ws is None:
-        ws = torch.zeros(max(wsb, 1), dtype=torch.uint8, device=dev)
+        ws = torch.zeros(max(demand_workspace_bytes(R, T, k, n_experts), 1), dtype=torch.uint8, device=dev)
     _check(lib().vp_demand(_ptr(routing), R, T, k, n_experts, n_ranks, first_rank, sort_row, unit,
                            _ptr(out["counts"]), _ptr(out["demand"]), _ptr(out["sorted_tok"]),
                            _ptr(out.get("sorted_slot")), _ptr(out["dest_off"]), _ptr(status), _ptr(ws),
@@ -337,7 +339,7 @@ def receive_counts(words: torch.Tensor, word_stride: int, signal: torch.Tensor, 
         raise ValueError("words too short for N sources at this offset and stride")
     if out is None:
         out = torch.empty((N, n_local), dtype=torch.int32, device=signal.device)
-    _check(lib().vp_receive_counts(C.c_void_p(words.data_ptr() + 4 * offset), word_stride, _ptr(signal), N,
+    _check(lib().vp_receive_counts(words.data_ptr() + 4 * offset, word_stride, _ptr(signal), N,
                                    n_local, _ptr(out), _stream(stream)), "vp_receive_counts")
     return out
 
@@ -442,9 +444,8 @@ def plan_batch(cat: Catalog, D: torch.Tensor, p: PlanParams, status: Optional[to
         status = torch.zeros(B, dtype=torch.int32, device=D.device)
     if status.numel() != B:
         raise ValueError("status must hold B entries")
-    need = plan_batch_workspace_bytes(cat, p, B)
     if ws is None:
-        ws = torch.empty(need, dtype=torch.uint8, device=D.device)
+        ws = torch.empty(plan_batch_workspace_bytes(cat, p, B), dtype=torch.uint8, device=D.device)
     _check(lib().vp_plan_batch(cat.handle, B, _ptr(D), C.byref(p), _ptr(out["K"]), _ptr(out["family"]),
                                _ptr(out["dst"]), _ptr(out["inst"]), _ptr(out["bytes"]), _ptr(out.get("send_off")),
                                _ptr(out.get("stream_off")), _ptr(out.get("recv_src")), _ptr(out["tau"]),

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <exception>
 #include <new>
@@ -17,6 +18,20 @@ thread_local std::string g_last_error;
 vp_status set_error(vp_status s, const std::string& msg) {
   g_last_error = msg;
   return s;
+}
+
+vp_status device_lds(int* dev, size_t* lds) {
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];   // zero: not asked yet
+  if (hipGetDevice(dev) != hipSuccess) return set_error(VP_ERR_HIP, "hipGetDevice failed");
+  int v = *dev >= 0 && *dev < kDevices ? known[*dev].load(std::memory_order_relaxed) : 0;
+  if (v == 0) {
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, *dev) != hipSuccess)
+      return set_error(VP_ERR_HIP, "hipDeviceGetAttribute failed");
+    if (*dev >= 0 && *dev < kDevices) known[*dev].store(v, std::memory_order_relaxed);
+  }
+  *lds = (size_t)v;
+  return VP_OK;
 }
 
 }  // namespace vp

@@ -689,10 +689,19 @@ void build_device_image(vp_catalog& c) {
   L.kS = c.nn | 1;
   L.q_magic = Q == 1 ? 0u : (uint32_t)(((uint64_t(1) << 32) + (uint64_t)Q - 1) / (uint64_t)Q);
   int most = 1;   // intra-node lanes of a pattern
+  L.hmax = 1;
+  L.MLT = L.MRT = 0;
   for (int p = 0; p < P; ++p) {
-    int n = 0;
-    for (int x = 0; x < Q * Q; ++x) n += c.patL[p][x];
+    int n = 0, pairs = 0, nic = 0;   // a slot pair counts once per NIC lane on it (several NICs per switch)
+    for (int x = 0; x < Q * Q; ++x) {
+      n += c.patL[p][x];
+      pairs += c.patL[p][x] != 0;
+      nic += c.patR[p][x];
+    }
     most = std::max(most, n);
+    L.MLT = std::max(L.MLT, pairs);
+    L.MRT = std::max(L.MRT, nic);
+    L.hmax = std::max(L.hmax, c.pat_fe[p] - c.pat_fb[p]);
   }
   L.RW = (most + 7) / 8 * 8;
   auto r16 = [](int x) { return (x + 15) / 16 * 16; };

@@ -50,6 +50,8 @@ struct DevCatalogLayout {
   int32_t pl_end;        // bytes with the records
   int32_t max_sets;      // most sets of one wavefront
   uint32_t q_magic;      // ceil(2^32 / Q), for Q > 1: x / Q = umulhi(x, q_magic) for x < 2^16
+  int32_t hmax;          // most families of a pattern
+  int32_t MLT, MRT;      // most intra-node slot pairs and most NIC lanes of a pattern
   int32_t total;         // int32 elements
   int64_t bw_cls[4];     // rate of PIX, PXB, NIC, SYS paths
   int64_t bw_max;
@@ -80,6 +82,9 @@ struct vp_catalog {
 namespace vp {
 
 vp_status set_error(vp_status s, const std::string& msg);
+// Index and LDS per workgroup of the current device (the latter asked for
+// once per device); VP_OK or VP_ERR_HIP.
+vp_status device_lds(int* dev, size_t* lds);
 vp_status build_catalog_host(const vp_topology& t, vp_catalog& c);
 std::vector<uint8_t> serialize_catalog(const vp_catalog& c);
 vp_status restrict_catalog(const vp_catalog& in, int rule, vp_catalog& out);

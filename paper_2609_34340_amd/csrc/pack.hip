@@ -800,12 +800,11 @@ vp_status launch_pack(const PackLaunch& a, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   const size_t lds = slice_lds_bytes(a.k_max, a.N);
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return set_error(VP_ERR_HIP, "hipGetDevice failed");
-  int lds_max = 0;
-  if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-    return set_error(VP_ERR_HIP, "hipDeviceGetAttribute failed");
+  size_t lds_max = 0;
+  const vp_status ds = device_lds(&dev, &lds_max);
+  if (ds != VP_OK) return ds;
   const bool layout = a.send_off != nullptr;
-  if (!layout && lds + 1024 > (size_t)lds_max)
+  if (!layout && lds + 1024 > lds_max)
     return set_error(VP_ERR_UNSUPPORTED, "k_max too large for the slice table");
   if (a.unit % 16 != 0) return set_error(VP_ERR_INVALID_ARGUMENT, "unit must be a multiple of 16");
   if ((a.mode == 0) != (a.k > 0)) return set_error(VP_ERR_INVALID_ARGUMENT, "top-k must be > 0 exactly for rows");

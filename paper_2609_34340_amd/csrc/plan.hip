@@ -1600,17 +1600,8 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   // the kernel addresses one matrix's schedule with 32-bit byte offsets
   if ((uint64_t)a.p.k_max * (uint64_t)N * 8 >= (uint64_t(1) << 32))
     return set_error(VP_ERR_UNSUPPORTED, "k_max * N too large for the planner");
-  int hmax = 1, mrt = 0;
-  for (int p = 0; p < NP; ++p) {
-    hmax = std::max(hmax, c.pat_fe[p] - c.pat_fb[p]);
-    int nl = 0;
-    for (int v : c.patL[p]) nl += v != 0;
-    if (nl > kMaxLTerms) return set_error(VP_ERR_UNSUPPORTED, "too many intra-node lane classes");
-    int nr = 0;   // cross-node lanes (a slot pair counts once per lane: several NICs per switch)
-    for (int v : c.patR[p]) nr += v;
-    if (nr > kMaxRTerms) return set_error(VP_ERR_UNSUPPORTED, "too many NIC lanes in one pattern");
-    mrt = std::max(mrt, nr);
-  }
+  if (L.MLT > kMaxLTerms) return set_error(VP_ERR_UNSUPPORTED, "too many intra-node lane classes");
+  if (L.MRT > kMaxRTerms) return set_error(VP_ERR_UNSUPPORTED, "too many NIC lanes in one pattern");
 
   PlanArgs P{};
   P.cat = (const int32_t*)c.dev;
@@ -1634,7 +1625,7 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   P.odd_inv = inv;
   P.odd_lim = ~uint64_t(0) / u;
   P.n_start = NS;
-  P.MRT = mrt;
+  P.MRT = L.MRT;
   P.i_aa = a.p.i_aa;
   P.k_max = a.p.k_max;
   P.K = a.K;
@@ -1665,11 +1656,9 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   }
 
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return set_error(VP_ERR_HIP, "hipGetDevice failed");
-  int lds_max = 0;
-  if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-    return set_error(VP_ERR_HIP, "hipDeviceGetAttribute failed");
-  const size_t budget = (size_t)lds_max;
+  size_t budget = 0;
+  const vp_status ds = device_lds(&dev, &budget);
+  if (ds != VP_OK) return ds;
   // Catalogs the planner takes: the library's stated limit, the tables and
   // one family's whole working set (lists, credits, residuals and every
   // start's bindings) within one workgroup's LDS.  This kernel needs less.
@@ -1685,7 +1674,7 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
       need += align_up(x, 16);
     if (need > budget) return set_error(VP_ERR_UNSUPPORTED, "plan state does not fit in LDS");
   }
-  P.FC = std::min(hmax, kFamChunk);
+  P.FC = std::min(L.hmax, kFamChunk);
   size_t o = align_up(sizeof(Shared), 16);
   auto take = [&](int32_t* field, size_t bytes) {
     *field = (int32_t)o;
