@@ -23,6 +23,8 @@
 //                  counts scanned per expert.  Loads are unconditional
 //                  (clamped indexes, masked results) so that each wait
 //                  covers only the load it needs.
+//   demand_small   instead of both for rows of up to 4,096 ids and up to
+//                  1,024 experts: one workgroup per row.
 //   No workgroup waits for another: the kernel boundary publishes pass 1.
 //   control_words / receive_counts  the sparse expert-parallel control word
 //                 of every (source, destination) pair from the counts, and
@@ -225,6 +227,60 @@ __device__ inline int32_t block_excl_scan(int32_t* v, int n, int32_t* wtot) {
   return all;
 }
 
+// Stable ranks of a wavefront's ids among its ids of the same expert, ids in
+// order (m, lane) from position `base` of a row of Tk; `mine` counts them per
+// expert (zero on entry).  Ids past the row become -1.
+template <int kPT>
+__device__ inline void rank_ids(int (&ev)[kPT], int (&rk)[kPT], int64_t base, int64_t Tk, int E, int bits,
+                                int32_t* mine, int lane) {
+  // Match masks of all kPT ids at once, bit by bit of the expert id: the kPT
+  // ballots of one bit are independent, so their latencies overlap.  Ids
+  // past the row (and bad ids) are no ids.
+  uint64_t same[kPT];
+#pragma unroll
+  for (int m = 0; m < kPT; ++m) {
+    if (base + m * 64 + lane >= Tk) ev[m] = -1;
+    same[m] = __ballot((unsigned)ev[m] < (unsigned)E);
+  }
+  for (int bt = 0; bt < bits; ++bt) {
+#pragma unroll
+    for (int m = 0; m < kPT; ++m) {
+      const bool one = ((uint32_t)ev[m] >> bt) & 1u;
+      const uint64_t ones = __ballot(one);
+      same[m] &= one ? ones : ~ones;
+    }
+  }
+  // The wave's running count of each expert: id m's rank is the count before
+  // it plus its lower lanes with the same expert; the lowest lane of each
+  // group then adds the group's size.  The adds return nothing and the
+  // wave's LDS operations complete in order, so no id waits for the one
+  // before it; the counts read are summed after the last add.
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  int cnt_before[kPT];
+#pragma unroll
+  for (int m = 0; m < kPT; ++m) {
+    const int e = ev[m];
+    const bool ok = (unsigned)e < (unsigned)E;
+    const uint64_t below = same[m] & lt;
+    rk[m] = __popcll(below);
+    cnt_before[m] = mine[ok ? e : 0];
+    wave_sync();
+    if (ok && below == 0)
+      __hip_atomic_fetch_add(&mine[e], (int32_t)__popcll(same[m]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    wave_sync();
+  }
+#pragma unroll
+  for (int m = 0; m < kPT; ++m) rk[m] += cnt_before[m];
+}
+
+// Token and routing slot of assignment x, written at position `at` of the
+// sorted row: x < 2^31 and k < 256, the multiply-high quotient is exact.
+__device__ inline void store_sorted(const DemandArgs& a, uint32_t x, int at) {
+  const uint32_t t = (uint32_t)__umul64hi((uint64_t)x << 24, a.k_magic);
+  a.sorted_tok[at] = (int32_t)t;
+  if (a.sorted_slot) a.sorted_slot[at] = (uint8_t)(x - t * (uint32_t)a.k);
+}
+
 // Pass 2.  Workgroup c < nch places the ids of sort chunk c; the R
 // workgroups after them merge their row's parts into its counts and demand
 // row.  A chunk's offsets: expert e starts at the total of the experts below
@@ -314,44 +370,8 @@ __global__ void __launch_bounds__(TH) demand_finish(DemandArgs a) {
   int32_t* mine = wc + w * E;
   for (int e = lane; e < E; e += 64) mine[e] = 0;
   wave_sync();
-  // Match masks of all kPT ids at once, bit by bit of the expert id: the kPT
-  // ballots of one bit are independent, so their latencies overlap.  Ids
-  // past the row (and bad ids) are no ids.
-  uint64_t same[kPT];
-#pragma unroll
-  for (int m = 0; m < kPT; ++m) {
-    if (base + m * 64 + lane >= a.Tk) ev[m] = -1;
-    same[m] = __ballot((unsigned)ev[m] < (unsigned)E);
-  }
-  for (int bt = 0; bt < a.bits; ++bt) {
-#pragma unroll
-    for (int m = 0; m < kPT; ++m) {
-      const bool one = ((uint32_t)ev[m] >> bt) & 1u;
-      const uint64_t ones = __ballot(one);
-      same[m] &= one ? ones : ~ones;
-    }
-  }
-  // The wave's running count of each expert: id m's rank is the count before
-  // it plus its lower lanes with the same expert; the lowest lane of each
-  // group then adds the group's size.  The adds return nothing and the
-  // wave's LDS operations complete in order, so no id waits for the one
-  // before it; the counts read are summed after the last add.
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  int rk[kPT], cnt_before[kPT];
-#pragma unroll
-  for (int m = 0; m < kPT; ++m) {
-    const int e = ev[m];
-    const bool ok = (unsigned)e < (unsigned)E;
-    const uint64_t below = same[m] & lt;
-    rk[m] = __popcll(below);
-    cnt_before[m] = mine[ok ? e : 0];
-    wave_sync();
-    if (ok && below == 0)
-      __hip_atomic_fetch_add(&mine[e], (int32_t)__popcll(same[m]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    wave_sync();
-  }
-#pragma unroll
-  for (int m = 0; m < kPT; ++m) rk[m] += cnt_before[m];
+  int rk[kPT];
+  rank_ids<kPT>(ev, rk, base, a.Tk, E, a.bits, mine, lane);
   if (OFF != kOffScanned) {
     if (OFF == kOffHeld) {
       const int n4 = a.nch4 / 4;
@@ -421,17 +441,88 @@ __global__ void __launch_bounds__(TH) demand_finish(DemandArgs a) {
   int at[kPT];
 #pragma unroll
   for (int m = 0; m < kPT; ++m) at[m] = mine[(unsigned)ev[m] < (unsigned)E ? ev[m] : 0] + rk[m];
-  uint8_t* const slot_out = a.sorted_slot;
+#pragma unroll
+  for (int m = 0; m < kPT; ++m)
+    if ((unsigned)ev[m] < (unsigned)E) store_sorted(a, (uint32_t)(base + m * 64 + lane), at[m]);
+}
+
+// The whole demand in one launch, one workgroup per row, for rows of up to
+// 512 kPT ids and up to kSmallExperts experts: bound by the latency of one
+// chain (ids, counts, offsets, stores), which the two passes walk twice with a
+// launch between them.  The sorted row's wavefronts rank their ids, so their
+// counts are the row's; the others count by LDS atomics.  Measured, two passes
+// against one launch (graph replays): 768 ids 7.4 -> 4.0 us (one row and 64
+// alike), 256 rows of 2,048 ids 8.7 -> 5.6, of 4,096 ids 10.0 -> 8.9, 8 rows of
+// 4,096 ids 7.8 -> 7.3.  The gain ends there: beyond, one workgroup issues all
+// of a row's scattered stores (32,768 ids 11 us in two passes, 50 in one).
+constexpr int kSmallThreads = 512;
+constexpr int kSmallExperts = 1024;
+
+template <int kPT>
+__global__ void __launch_bounds__(kSmallThreads) demand_small(DemandArgs a) {
+  constexpr int kW = kSmallThreads / 64;
+  extern __shared__ int32_t sh[];   // tot [E], wc [kW][E]
+  __shared__ int32_t wtot[kW];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, E = a.E, r = blockIdx.x;
+  const bool sorting = r == a.sort_row;
+  int32_t* tot = sh;
+  int32_t* wc = sh + E;
+  int32_t* mine = wc + w * E;
+  const int32_t* ids = a.routing + (size_t)r * a.Tk;
+  const int64_t base = (int64_t)w * 64 * kPT;
+  int ev[kPT], rk[kPT];
 #pragma unroll
   for (int m = 0; m < kPT; ++m) {
-    if ((unsigned)ev[m] < (unsigned)E) {
-      // x < 2^31 and k < 256: the multiply-high quotient is exact
-      const uint32_t x = (uint32_t)(base + m * 64 + lane);
-      const uint32_t t = (uint32_t)__umul64hi((uint64_t)x << 24, a.k_magic);
-      a.sorted_tok[at[m]] = (int32_t)t;
-      if (slot_out) slot_out[at[m]] = (uint8_t)(x - t * (uint32_t)a.k);
-    }
+    const int64_t x = base + m * 64 + lane;
+    ev[m] = a.Tk > 0 ? ids[x < a.Tk ? x : a.Tk - 1] : -1;
   }
+  for (int e = lane; e < E; e += 64) mine[e] = 0;
+  wave_sync();
+  bool bad = false;
+#pragma unroll
+  for (int m = 0; m < kPT; ++m) bad |= base + m * 64 + lane < a.Tk && (unsigned)ev[m] >= (unsigned)E;
+  if (bad) report(a.status, VP_ERR_INVALID_ARGUMENT);
+  if (sorting) {
+    rank_ids<kPT>(ev, rk, base, a.Tk, E, a.bits, mine, lane);
+  } else {
+#pragma unroll
+    for (int m = 0; m < kPT; ++m)
+      if (base + m * 64 + lane < a.Tk && (unsigned)ev[m] < (unsigned)E) atomicAdd(&mine[ev[m]], 1);
+  }
+  __syncthreads();
+  // totals; the sorted row's waves also get their start inside each expert
+  for (int e = tid; e < E; e += kSmallThreads) {
+    int32_t c = 0;
+#pragma unroll
+    for (int v = 0; v < kW; ++v) {
+      const int32_t x = wc[v * E + e];
+      if (sorting) wc[v * E + e] = c;
+      c += x;
+    }
+    a.counts[(size_t)r * E + e] = c;
+    tot[e] = c;
+  }
+  __syncthreads();
+  const int eloc = E / a.N, self = a.first_rank + r;
+  for (int j = tid; j < a.N; j += kSmallThreads) {
+    int64_t c = 0;
+    for (int e = j * eloc; e < (j + 1) * eloc; ++e) c += tot[e];
+    a.demand[(size_t)r * a.N + j] = j == self ? 0 : c * a.unit;
+  }
+  if (!sorting) return;
+  __syncthreads();
+  const int32_t total = block_excl_scan<kSmallThreads>(tot, E, wtot);
+  for (int j = tid; j < a.N; j += kSmallThreads) a.dest_off[j] = tot[j * eloc];
+  if (tid == 0) a.dest_off[a.N] = total;
+  int at[kPT];
+#pragma unroll
+  for (int m = 0; m < kPT; ++m) {
+    const int e = (unsigned)ev[m] < (unsigned)E ? ev[m] : 0;
+    at[m] = tot[e] + mine[e] + rk[m];
+  }
+#pragma unroll
+  for (int m = 0; m < kPT; ++m)
+    if ((unsigned)ev[m] < (unsigned)E) store_sorted(a, (uint32_t)(base + m * 64 + lane), at[m]);
 }
 
 __global__ void demand_heads_kernel(int64_t T, const int64_t* __restrict__ head_lo, int64_t head_bytes,
@@ -545,6 +636,18 @@ vp_status launch_demand(const DemandLaunch& a, void* stream) {
   DemandArgs d{a.routing, Tk, w.part, a.unit, a.E, a.N, a.first_rank, a.R, w.P, a.sort_row, w.nch, w.nch4, a.k,
                bits, k_magic, sorting && w.nch > kInBlockScan, a.counts, a.demand, a.sorted_tok, a.sorted_slot, a.dest_off,
                (int32_t*)ws, (int32_t*)(ws + partials), a.status};
+  // up to 4,096 ids per row: one launch (both sides measured at demand_small)
+  if (Tk <= 8 * kSmallThreads && a.E <= kSmallExperts) {
+    const size_t lds = (size_t)(1 + kSmallThreads / 64) * a.E * sizeof(int32_t);
+    if (Tk <= 2 * kSmallThreads)
+      hipLaunchKernelGGL(demand_small<2>, dim3((unsigned)a.R), dim3(kSmallThreads), lds, s, d);
+    else if (Tk <= 4 * kSmallThreads)
+      hipLaunchKernelGGL(demand_small<4>, dim3((unsigned)a.R), dim3(kSmallThreads), lds, s, d);
+    else
+      hipLaunchKernelGGL(demand_small<8>, dim3((unsigned)a.R), dim3(kSmallThreads), lds, s, d);
+    if (hipGetLastError() != hipSuccess) return set_error(VP_ERR_HIP, "demand launch failed");
+    return VP_OK;
+  }
   const int64_t blocks1 = (int64_t)a.R * w.P + (sorting ? w.nch : 0);
   if (blocks1 >= ((int64_t)1 << 31)) return set_error(VP_ERR_UNSUPPORTED, "too many histogram parts");
   hipLaunchKernelGGL(demand_count, dim3((unsigned)blocks1), dim3(kThreads), (size_t)kWaves * a.E * sizeof(int32_t),
