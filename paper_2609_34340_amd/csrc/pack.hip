@@ -37,6 +37,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "divide.h"
 #include "internal.h"
 
 namespace vp {
@@ -62,20 +63,6 @@ struct StepDesc {
   uint64_t h_m40;  // heads: ceil(2^40 / h), for the gather's 32-bit divisions by h
   uint64_t h_m64;  // heads: ceil(2^64 / h), 0 for h = 1, for its 64-bit ones
 };
-
-// floor(x / d) for 0 <= x < 2^53 and 1 <= d < 2^53, without a 64-bit
-// integer division: the correctly rounded double quotient is within one of
-// it (below 2^52), and one step against the integer remainder makes it
-// exact.  Callers that cannot bound x check q * d against x.
-__host__ __device__ inline int64_t fdiv53(int64_t x, int64_t d) {
-  int64_t q = (int64_t)((double)x / (double)d);
-  const int64_t r = x - q * d;
-  if (r < 0)
-    --q;
-  else if (r >= d)
-    ++q;
-  return q;
-}
 
 // Multiply-high reciprocals of a divisor 1 <= d < 2^20 (see StepDesc):
 // ceil(2^40 / d), and ceil(2^64 / d) = 2^24 floor(2^40 / d) + the rest,

@@ -54,6 +54,7 @@
 #include <mutex>
 #include <string>
 
+#include "divide.h"
 #include "internal.h"
 
 namespace vp {
@@ -265,18 +266,6 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0), other counters untouched
   __builtin_amdgcn_s_barrier();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-// floor(x / d) for x >= 0, d >= 1: below 2^52 the correctly rounded double
-// quotient is within one of it, and one step against the remainder makes it
-// exact; larger values take the integer division.
-__device__ inline int64_t floor_div(int64_t x, int64_t d) {
-  if (x >= (int64_t(1) << 52) || d >= (int64_t(1) << 52)) return x / d;
-  int64_t q = (int64_t)((double)x / (double)d);
-  const int64_t r = x - q * d;
-  if (r < 0) --q;
-  else if (r >= d) ++q;
-  return q;
 }
 
 // mask ? a : b, bit by bit
@@ -558,12 +547,12 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
   uint32_t cap_p = 1, cap_n = 1;   // units
   {
     const int64_t den = L.bw_max * P.k_target;
-    tau = floor_div(Lmax + den - 1, den);
+    tau = exact_div(Lmax + den - 1, den);
     if (tau < 1) tau = 1;
     bool over = false;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      int64_t cu = floor_div(tau * L.bw_cls[c ? VP_PATH_NIC : VP_PATH_PIX], P.unit);
+      int64_t cu = exact_div(tau * L.bw_cls[c ? VP_PATH_NIC : VP_PATH_PIX], P.unit);
       if (cu < 1) cu = 1;
       // credits are int32 units below 2^27; a lane's bytes stay below 2^31
       over |= cu >= (int64_t(1) << 27) || cu * P.unit >= (int64_t(1) << 31);
