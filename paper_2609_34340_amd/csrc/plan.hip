@@ -40,7 +40,7 @@
 // matrix fits beside the tables (up to 160 ranks or so), in the caller's
 // workspace otherwise.  No host round trip happens between iterations.
 //
-// Measured, per activation: 2.15-2.25 us at 8 to 128 ranks and 3.6 us at 256 (16
+// Measured, per activation: 2.1-2.2 us at 8 to 128 ranks and 3.4 us at 256 (16
 // wavefronts, five barriers, the family's lists and credits staged in LDS for
 // the runs, schedule stores by the winner's wavefronts: 4.6-4.9 and 6.3 us).
 // A wavefront alone on its SIMD issues a dependent vector or scalar
@@ -672,7 +672,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
 #pragma unroll
     for (int r = 0; r < MG; ++r) {
       const int at = (lf * Q + gq[r]) * g;
-      if (P.rec_lds) {
+      if (__builtin_expect(P.rec_lds, 1)) {
 #pragma unroll
         for (int m = 0; m < g; ++m) {
           rec[r][m] = ((const uint32_t*)(tab + L.pl_recs))[at + m];
@@ -1184,7 +1184,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
   };
 
   while (err == 0 && rem != 0) {
-    if (K >= P.k_max) {
+    if (__builtin_expect(K >= P.k_max, 0)) {
       err = VP_ERR_CAPACITY;
       break;
     }
@@ -1197,7 +1197,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     if (kprev != 0 && ns > 0) {
       // a set's best shift changes only with the column of the last
       // activation's shift
-      if (P.held) {
+      if (__builtin_expect(P.held, 1)) {
         if (kprev > 0) {
           const int u0 = kprev - k0;   // an idle lane's sums are not used
           const int32_t s = shift_sum(kprev);
@@ -1262,9 +1262,9 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     {
       // candidate of a pattern: {score, shape code, payload}, compared by
       // score, then by the lower code
-      uint2 r = rb[info0.x >> 16];
+      const uint2 r = rb[info0.x >> 16];
       uint32_t sc = (uint32_t)(a0[0] + a0[1] + a0[2] + a0[3] + a0[4] + a0[5] + a0[6] + a0[7]);
-      if (RW8 > 1)
+      if (__builtin_expect(RW8 > 1, 0))
         for (int m = 1; m < RW8; ++m) {
           const uint4 t = rows[min(ib + lane, L.J0 + L.J1 - 1) * RW8 + m];
 #pragma unroll
@@ -1272,21 +1272,36 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         }
       uint32_t code = (r.y << 12) | (info0.x & 0xFFFF), pay = info0.y;
       sc = ib + lane < ie ? sc + r.x : 0;
-      for (int u = 1; u < nitem; ++u) {
-        const int it = ib + lane + 64 * u, ic = min(it, ie - 1);
-        const uint2 inf = info[ic];
-        r = rb[inf.x >> 16];
-        uint32_t s = r.x;
-        for (int m = 0; m < RW8; ++m) {
-          const uint4 t = rows[ic * RW8 + m];
+      if (__builtin_expect(nitem > 1, 0)) {
+        // a round's rows and sets are asked for one round ahead (cross-socket
+        // nodes have five: 4.07 us per activation without, 3.5 with)
+        uint4 t_next;
+        uint2 inf_next;
+        auto fetch_item = [&](int it) {
+          const int ic = min(it, ie - 1);
+          t_next = rows[ic * RW8];
+          inf_next = info[ic];
+        };
+        fetch_item(ib + lane + 64);
+        for (int it = ib + lane + 64; it - lane < ie; it += 64) {
+          const uint4 t = t_next;
+          const uint2 inf = inf_next, rs = rb[inf.x >> 16];
+          int32_t v[8];
 #pragma unroll
-          for (int x = 0; x < 8; ++x) s += (uint32_t)row_of(t, x)[0];
-        }
-        const uint32_t c = (r.y << 12) | (inf.x & 0xFFFF);
-        if (it < ie && (s > sc || (s == sc && c < code))) {
-          sc = s;
-          code = c;
-          pay = inf.y;
+          for (int x = 0; x < 8; ++x) v[x] = *row_of(t, x);
+          fetch_item(it + 64);
+          uint32_t s = rs.x + (uint32_t)(v[0] + v[1] + v[2] + v[3] + v[4] + v[5] + v[6] + v[7]);
+          for (int m = 1; m < RW8; ++m) {
+            const uint4 tm = rows[min(it, ie - 1) * RW8 + m];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) s += (uint32_t)row_of(tm, x)[0];
+          }
+          s = it < ie ? s : 0;
+          const uint32_t c = (rs.y << 12) | (inf.x & 0xFFFF);
+          const bool take = s > sc || (s == sc && c < code);
+          sc = take ? s : sc;
+          code = take ? c : code;
+          pay = take ? inf.y : pay;
         }
       }
       // the wavefront's best, or its equals, to the workgroup's argmax
@@ -1300,7 +1315,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     else __syncthreads();
     VP_STAMP(3);
     const uint64_t key = (uint64_t)lane0((int64_t)sh->key[K & 1]), step_key = (uint64_t)lane0((int64_t)sh->step_key[K & 1]);
-    if (key == 0) {
+    if (__builtin_expect(key == 0, 0)) {
       err = VP_ERR_NO_PROGRESS;
       break;
     }
@@ -1331,7 +1346,10 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
 
     // Steps 2-4 over the shape's families
     uint32_t best_F;
-    if ((key & 0x1000) == 0 && NS <= kSlots) {
+    // (The probability only places the code.  As all but certain it took a
+    // further 5 % off 256 ranks, but put 10 % on shapes of many families.)
+    const bool one_family = (key & 0x1000) == 0 && NS <= kSlots;
+    if (MG > 1 ? __builtin_expect(one_family, 1) : __builtin_expect_with_probability(one_family, 1, 0.6)) {
       // one family, one start per wavefront: the first start with the highest
       // score wins, no utility to compare
       const int lf = (int)(key & 0xFFF);
@@ -1488,7 +1506,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
       }
       lf_prev = lb + best_c;
     }
-    if (best_F == 0) {
+    if (__builtin_expect(best_F == 0, 0)) {
       err = VP_ERR_NO_PROGRESS;
       break;
     }
