@@ -28,7 +28,6 @@
 
 #include <algorithm>
 
-#include "divide.h"
 #include "internal.h"
 
 namespace vp {
@@ -40,9 +39,8 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 __device__ inline void report(int32_t* status, int code) { atomicCAS(status, 0, code); }
 
-constexpr int kMapThreads = 512;
+constexpr int kMapThreads = 256;
 constexpr int kMapWaves = kMapThreads / 64;
-constexpr int kMapRows = 4;   // rows of a slice that a thread has in flight
 
 struct MapArgs {
   int mode, self, N, k_max, eloc, E, k;
@@ -61,22 +59,15 @@ struct MapArgs {
   int32_t* status;
 };
 
-// Sums of two values over the block; every thread gets them.
-__device__ void block_sum2(int64_t& u, int64_t& v, int64_t (*red)[2]) {
-  for (int o = 32; o > 0; o >>= 1) {
-    u += __shfl_xor(u, o);
-    v += __shfl_xor(v, o);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6][0] = u;
-    red[threadIdx.x >> 6][1] = v;
-  }
+// Sum over the block; every thread gets it.
+__device__ int64_t block_sum(int64_t v, int64_t* red) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   __syncthreads();
-  u = v = 0;
-  for (int i = 0; i < kMapWaves; ++i) {
-    u += red[i][0];
-    v += red[i][1];
-  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  int64_t s = 0;
+  for (int i = 0; i < kMapWaves; ++i) s += red[i];
+  return s;
 }
 
 // Exclusive scan of v[0, n) in LDS by the whole block; returns the total.
@@ -108,49 +99,15 @@ __device__ int64_t block_excl_scan(int64_t* v, int n, int64_t* red) {
   return total;
 }
 
-// Bound by latency, a chain of dependent loads: the lanes of this rank in this
-// and the earlier steps, then their volumes, then the rows.  The first round
-// of every load is issued before anything is waited for (the schedule arrays
-// have k_max rows, so also before K is known; indexes taken from them are
-// clamped and the results masked), volumes are divided in floating point, and
-// the experts of one rank are scanned by one wavefront.  16 ranks, 49 steps,
-// up to 117,000 rows: 16.0 us with one load waited for at a time, 9.7 us now.
 __global__ void __launch_bounds__(kMapThreads) map_kernel(MapArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int64_t red2[kMapWaves][2], red[kMapWaves];
+  __shared__ int64_t red[kMapWaves];
   __shared__ int32_t sK, sst;
-  const int k = blockIdx.x, tid = threadIdx.x, N = a.N, self = a.self, eloc = a.eloc;
-  const bool recv = a.mode != kModeCombinePack, experts = a.mode != kModeCombineUnpack;
+  const int k = blockIdx.x, tid = threadIdx.x, N = a.N, self = a.self;
   if (tid == 0) {   // one read, so that every early exit below is taken by the whole block
     sK = *a.Kp;
     sst = *a.status;
   }
-  int64_t* tot = (int64_t*)smem;   // [N] rows per peer (last step only)
-  // expert-major output: expert m's rows start at base[m] = rows of experts
-  // before m from every source + rows of m from sources before the peer; the
-  // peer's stream holds its rows for expert m from cum[m] on
-  int64_t* base = tot + N;         // [eloc]
-  int64_t* part = base + eloc;     // [eloc]
-  int64_t* cum = part + eloc;      // [eloc + 1]
-  // this step's lane and the one of step tid: the rank whose lane lands here,
-  // or this rank's destination
-  const int32_t* lanes = recv ? a.recv_src : a.dst;
-  const int kt = min(tid, a.k_max - 1);
-  const int lane_raw = lanes[(size_t)k * N + self], lane_t = lanes[(size_t)kt * N + self];
-  const int n_cnt = experts ? N * eloc : 0;
-  int32_t cnt0 = 0;   // the first round of the counts of this rank's experts
-  if (tid < n_cnt) cnt0 = a.counts[(size_t)(tid / eloc) * a.E + (size_t)self * eloc + tid % eloc];
-  for (int j = tid; j < N; j += kMapThreads) tot[j] = 0;
-  if (experts)
-    for (int m = tid; m < eloc; m += kMapThreads) base[m] = part[m] = 0;
-  // 1. this step: the lane carrying rows to or from this rank, and its peer
-  bool ok = lane_raw >= 0 && lane_raw < N;
-  const int peer = ok ? lane_raw : 0, src = recv ? peer : self;
-  const int64_t x = a.bytes[(size_t)k * N + src];
-  const int back = a.dst[(size_t)k * N + src];
-  const int peer_t = lane_t >= 0 && lane_t < N ? lane_t : 0, src_t = recv ? peer_t : self;
-  const int64_t x_t = a.bytes[(size_t)kt * N + src_t];
-  const int back_t = a.dst[(size_t)kt * N + src_t];
   __syncthreads();
   const int K = sK;
   if (K < 0 || K > a.k_max) {
@@ -165,127 +122,137 @@ __global__ void __launch_bounds__(kMapThreads) map_kernel(MapArgs a) {
     }
     return;
   }
-  ok = ok && (!recv || back == self) && x >= 0 && (x == 0 || peer != self);
-  const int64_t nu = ok ? exact_div(x, a.rb) : 0;
-  if (!ok || nu * a.rb != x) {
+  const bool recv = a.mode != kModeCombinePack;
+
+  // 1. this step: the lane carrying rows to or from this rank, and its peer
+  int lane_k, peer;
+  bool ok;
+  if (recv) {
+    lane_k = a.recv_src[(size_t)k * N + self];
+    ok = lane_k >= 0 && lane_k < N && a.dst[(size_t)k * N + lane_k] == self;
+    peer = lane_k;
+  } else {
+    lane_k = self;
+    peer = a.dst[(size_t)k * N + self];
+    ok = peer >= 0 && peer < N;
+  }
+  const int64_t x = ok ? a.bytes[(size_t)k * N + lane_k] : 0;
+  ok = ok && x >= 0 && x % a.rb == 0 && (x == 0 || peer != self);
+  if (!ok) {
     if (tid == 0) report(a.status, VP_ERR_INVALID_ARGUMENT);
     return;
   }
 
-  // 2. rows of this rank's earlier steps, in total and with the same peer;
-  //    the last step's workgroup also counts every peer's rows.  A lane that
-  //    does not match the schedule, or not whole rows, is reported by its
-  //    step's own workgroup and left out here.
+  // 2. volumes of this rank's earlier steps, in total and with the same peer;
+  //    the last step's workgroup also counts every peer's rows
   const bool last = k == K - 1;
-  int64_t g0 = 0, q0 = 0;
+  int64_t* tot = (int64_t*)smem;   // [N] rows per peer (last step only)
+  if (last)
+    for (int j = tid; j < N; j += kMapThreads) tot[j] = 0;
+  __syncthreads();
+  int64_t pos = 0, strm = 0;
   const int kend = last ? K : k;
-  auto earlier = [&](int kk, int lane_kk, int p, int64_t xx, int bk) {
-    if (lane_kk < 0 || lane_kk >= N || (recv && bk != self)) return;
-    const int64_t rows = exact_div(xx, a.rb);
-    if (kk < k) {
-      g0 += rows;
-      if (p == peer) q0 += rows;
+  for (int kk = tid; kk < kend; kk += kMapThreads) {
+    int s = self, p;
+    if (recv) {
+      s = a.recv_src[(size_t)kk * N + self];
+      p = s;
+    } else {
+      p = a.dst[(size_t)kk * N + self];
     }
-    if (last && xx > 0) atomicAdd((unsigned long long*)&tot[p], (unsigned long long)rows);
-  };
-  if (tid < kend) earlier(tid, lane_t, peer_t, x_t, back_t);
-  for (int kk = tid + kMapThreads; kk < kend; kk += kMapThreads) {
-    const int l = lanes[(size_t)kk * N + self], p = l >= 0 && l < N ? l : 0, s = recv ? p : self;
-    earlier(kk, l, p, a.bytes[(size_t)kk * N + s], a.dst[(size_t)kk * N + s]);
+    // a lane that does not match the schedule is reported by its step's own
+    // workgroup and left out here
+    if (s < 0 || s >= N || p < 0 || p >= N || (recv && a.dst[(size_t)kk * N + s] != self)) continue;
+    const int64_t xx = a.bytes[(size_t)kk * N + s];
+    if (kk < k) {
+      pos += xx;
+      if (p == peer) strm += xx;
+    }
+    if (last && xx > 0) atomicAdd((unsigned long long*)&tot[p], (unsigned long long)(xx / a.rb));
   }
+  pos = block_sum(pos, red);
+  strm = block_sum(strm, red);
+  const int64_t g0 = pos / a.rb, nu = x / a.rb, q0 = strm / a.rb;
+  if (tid == 0) {
+    if (a.step_off) a.step_off[k] = pos;
+    if (last) {
+      *a.total = g0 + nu;
+      if (a.step_off) a.step_off[K] = pos + x;
+    }
+  }
+  if (pos < 0 || strm < 0 || g0 + nu > a.rows_cap) {
+    if (tid == 0) report(a.status, pos < 0 || strm < 0 ? VP_ERR_INVALID_ARGUMENT : VP_ERR_CAPACITY);
+    return;
+  }
+
   // 3. last step: every peer's stream must be delivered whole -- the rows of
   //    the peer's assignments to this rank's experts (dispatch receive, and the
   //    same rows sent back by the combine), or this rank's rows for that peer
-  //    (combine receive).  And the expert totals.
-  for (int idx = tid; idx < n_cnt; idx += kMapThreads) {
-    const int i = idx / eloc, m = idx - i * eloc;
-    const int64_t c = idx == tid ? cnt0 : a.counts[(size_t)i * a.E + (size_t)self * eloc + m];
-    if (last && i != self) atomicAdd((unsigned long long*)&tot[i], (unsigned long long)-c);
-    atomicAdd((unsigned long long*)&base[m], (unsigned long long)c);
-    if (i < peer) atomicAdd((unsigned long long*)&part[m], (unsigned long long)c);
-    if (i == peer) cum[m] = c;
-  }
-  if (last && !experts)
-    for (int p = tid; p < N; p += kMapThreads)
-      if (p != self)
-        atomicAdd((unsigned long long*)&tot[p], (unsigned long long)-(a.dest_off[p + 1] - a.dest_off[p]));
-  int64_t b0 = 0, len = 0;   // combine receive: the peer's rows in the sorted lists
-  if (!experts) {
-    b0 = a.dest_off[peer];
-    len = a.dest_off[peer + 1] - b0;
-  }
-  block_sum2(g0, q0, red2);
-  if (tid == 0) {
-    if (a.step_off) a.step_off[k] = g0 * a.rb;
-    if (last) {
-      *a.total = g0 + nu;
-      if (a.step_off) a.step_off[K] = g0 * a.rb + x;
+  //    (combine receive)
+  if (last) {
+    if (a.mode == kModeCombineUnpack) {
+      for (int p = tid; p < N; p += kMapThreads)
+        if (p != self)
+          atomicAdd((unsigned long long*)&tot[p], (unsigned long long)-(a.dest_off[p + 1] - a.dest_off[p]));
+    } else {
+      const int n = N * a.eloc;
+      for (int idx = tid; idx < n; idx += kMapThreads) {
+        const int p = idx / a.eloc, m = idx - p * a.eloc;
+        if (p != self)
+          atomicAdd((unsigned long long*)&tot[p],
+                    (unsigned long long)-(int64_t)a.counts[(size_t)p * a.E + (size_t)self * a.eloc + m]);
+      }
     }
-  }
-  if (last)
+    __syncthreads();
     for (int p = tid; p < N; p += kMapThreads)
       if (tot[p] != 0) report(a.status, VP_ERR_INVALID_ARGUMENT);
-  if (g0 < 0 || q0 < 0 || g0 > a.rows_cap || nu > a.rows_cap - g0) {
-    if (tid == 0) report(a.status, g0 < 0 || q0 < 0 ? VP_ERR_INVALID_ARGUMENT : VP_ERR_CAPACITY);
-    return;
   }
   if (nu == 0) return;
 
   // 4. the row on the other side of every row of this slice
-  if (!experts) {
-    if (b0 < 0 || len < 0 || b0 > a.map_cap || len > a.map_cap - b0 || q0 > len || nu > len - q0) {
-      if (tid == 0) report(a.status, VP_ERR_INVALID_ARGUMENT);   // sorted lists hold T * k entries
+  if (a.mode == kModeCombineUnpack) {
+    const int64_t b0 = a.dest_off[peer], len = a.dest_off[peer + 1] - b0;
+    if (b0 < 0 || len < 0 || b0 + len > a.map_cap || q0 + nu > len) {   // sorted lists hold T * k entries
+      if (tid == 0) report(a.status, VP_ERR_INVALID_ARGUMENT);
       return;
     }
-    const int32_t* tok = a.sorted_tok + b0 + q0;
-    const uint8_t* slot = a.sorted_slot + b0 + q0;
-    for (int64_t u0 = tid; u0 < nu; u0 += kMapRows * kMapThreads) {
-      int32_t t[kMapRows];
-      int c[kMapRows];
-#pragma unroll
-      for (int m = 0; m < kMapRows; ++m) {
-        const int64_t u = min(u0 + m * kMapThreads, nu - 1);
-        t[m] = tok[u];
-        c[m] = slot[u];
+    for (int64_t u = tid; u < nu; u += kMapThreads) {
+      const int64_t p = b0 + q0 + u;
+      const int64_t t = a.sorted_tok[p];
+      const int c = a.sorted_slot[p];
+      if (t < 0 || t >= a.T || c >= a.k) {
+        report(a.status, VP_ERR_INVALID_ARGUMENT);
+        continue;
       }
-#pragma unroll
-      for (int m = 0; m < kMapRows; ++m) {
-        const int64_t u = u0 + m * kMapThreads;
-        if (u >= nu) break;
-        if (t[m] < 0 || t[m] >= a.T || c[m] >= a.k) report(a.status, VP_ERR_INVALID_ARGUMENT);
-        else a.map[g0 + u] = (int32_t)((int64_t)t[m] * a.k + c[m]);
-      }
+      a.map[g0 + u] = (int32_t)(t * a.k + c);
     }
     return;
   }
-  int64_t out_rows, stream_rows;
-  if (eloc <= 64) {   // both scans in every wavefront; the first one leaves them in LDS
-    const int lane = tid & 63;
-    const int64_t bv = lane < eloc ? base[lane] : 0, cv = lane < eloc ? cum[lane] : 0;
-    int64_t bi = bv, ci = cv;
-    for (int o = 1; o < eloc; o <<= 1) {
-      const int64_t by = __shfl_up(bi, o), cy = __shfl_up(ci, o);
-      if (lane >= o) {
-        bi += by;
-        ci += cy;
-      }
-    }
-    out_rows = __shfl(bi, eloc - 1);
-    stream_rows = __shfl(ci, eloc - 1);
-    __syncthreads();
-    if (tid < eloc) {
-      base[tid] = bi - bv;
-      cum[tid] = ci - cv;
-    }
-    __syncthreads();
-  } else {
-    out_rows = block_excl_scan(base, eloc, red);
-    stream_rows = block_excl_scan(cum, eloc, red);
+  // expert-major output: expert m's rows start at base[m] = rows of experts
+  // before m from every source + rows of m from sources before the peer; the
+  // peer's stream holds its rows for expert m from cum[m] on
+  const int eloc = a.eloc;
+  int64_t* base = (int64_t*)smem + N;   // [eloc]
+  int64_t* part = base + eloc;          // [eloc]
+  int64_t* cum = part + eloc;           // [eloc + 1]
+  for (int m = tid; m < eloc; m += kMapThreads) {
+    base[m] = 0;
+    part[m] = 0;
+    cum[m] = a.counts[(size_t)peer * a.E + (size_t)self * eloc + m];
   }
-  if (q0 > stream_rows || nu > stream_rows - q0 || out_rows > a.map_cap) {
-    if (tid == 0)
-      report(a.status, out_rows > a.map_cap && !(q0 > stream_rows || nu > stream_rows - q0) ? VP_ERR_CAPACITY
-                                                                                            : VP_ERR_INVALID_ARGUMENT);
+  __syncthreads();
+  const int n = N * eloc;
+  for (int idx = tid; idx < n; idx += kMapThreads) {
+    const int i = idx / eloc, m = idx - i * eloc;
+    const int64_t c = a.counts[(size_t)i * a.E + (size_t)self * eloc + m];
+    atomicAdd((unsigned long long*)&base[m], (unsigned long long)c);
+    if (i < peer) atomicAdd((unsigned long long*)&part[m], (unsigned long long)c);
+  }
+  __syncthreads();
+  const int64_t out_rows = block_excl_scan(base, eloc, red);
+  const int64_t stream_rows = block_excl_scan(cum, eloc, red);
+  if (q0 + nu > stream_rows || out_rows > a.map_cap) {
+    if (tid == 0) report(a.status, q0 + nu > stream_rows ? VP_ERR_INVALID_ARGUMENT : VP_ERR_CAPACITY);
     return;
   }
   for (int64_t u = tid; u < nu; u += kMapThreads) {
