@@ -1399,7 +1399,9 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
       while (true) {
         int job = redo ? (best_c - best_chunk) * NS + best_s : j0 + slot;
         const bool runs = redo ? slot == win_slot : job < nc * NS;
-        if (S == 2) job = min(job, nc * NS - 1);   // the wavefronts stay in step
+        // past the chunk's last job a slot repeats it, so that the wavefronts stay in step; the winner's job counts
+        // in its own chunk, which may be longer than the last one
+        if (S == 2 && !redo) job = min(job, nc * NS - 1);
         const int cj = job / NS, start = job - cj * NS;
         Binding B;
         if (S == 2 || runs) {

@@ -4,6 +4,8 @@ D^rem and the family records in LDS or in global memory, sums of shifts held
 in registers or made again, one round of starts or several (a winner whose
 wavefront has run another job since runs again), shapes of one family and of
 many, patterns in one round of lanes or several."""
+import struct
+
 import numpy as np
 import pytest
 import torch
@@ -106,3 +108,65 @@ def test_rounds_of_starts(vp, topo, n_start):
     N = topo.n_ranks
     D = sparse_demand(rng, N, 3.0, 12)
     check(vp, topo, D, n_start=n_start, i_aa=[8, 0, 1, 2][n_start % 4], seed=n_start)
+
+
+def cut_catalog(vp, topo, begin, end):
+    """The catalog of `topo` with its shift-0 part cut to the families begin ... end - 1 (vp_catalog_load takes any
+    subset): magic and topology (48 bytes), family counts of both parts and lanes per node (12), one byte per lane,
+    FNV-1a of it all."""
+    p = vp.Catalog(topo).save()
+    f0, f1, lanes = struct.unpack_from("<3i", p, 48)
+    body = p[:48] + struct.pack("<3i", end - begin, f1, lanes) + p[60 + begin * lanes:60 + end * lanes] + \
+        p[60 + f0 * lanes:-8]
+    h = 0xcbf29ce484222325
+    for x in body:
+        h = (h ^ x) * 0x100000001b3 & 0xFFFFFFFFFFFFFFFF
+    return vp.Catalog.load(body + struct.pack("<Q", h))
+
+
+# A shape of 144 families (chunks of 64, 64 and 16) whose starts take two wavefronts each: the winner's chunk is not the
+# last one, so its run is made again.  One start without draws, so that the families' numbers in the cut catalog do not
+# matter, and the oracle's binding of the same shape of the whole catalog is the one to find.
+@pytest.mark.parametrize("i_aa", [8])
+def test_winner_in_an_earlier_chunk(vp, i_aa):
+    topo = vpgen.Topology(43, 1, 3, 2, 2)
+    o = oracle.Catalog(topo)
+    s = o.shapes()
+    shape = int(np.argmax(s["fam_end"] - s["fam_begin"]))
+    begin, end = int(s["fam_begin"][shape]), int(s["fam_end"][shape])
+    assert end - begin == 144 and s["k"][shape] == 0
+    cat = cut_catalog(vp, topo, begin, end)
+    cat.upload()
+    N, tab = o.N, cat.instances()
+    rank = np.arange(N)
+    node, switch, slot = rank // 6, rank // 2, rank // 2 % 3
+    local = (node[:, None] == node[None]) & (switch[:, None] != switch[None])
+    past_the_last = 0
+    for seed in range(12):
+        rng = np.random.default_rng(seed)
+        D = (rng.integers(0, 200, (N, N)) * local * UNIT).astype(np.int64)
+        cands, chosen = o.shape_candidates(D, UNIT, shape, k_target=8, n_start=1, i_aa=i_aa)
+        past_the_last += chosen - begin < 128 and (chosen - begin) % 64 >= 16
+        p = vp.plan_params(N, UNIT, k_target=8, n_start=1, i_aa=i_aa, k_max=4 * N)
+        st = vp.new_status()
+        out = vp.plan(cat, torch.from_numpy(D).cuda(), p, status=st)
+        torch.cuda.synchronize()
+        print("i_aa=%d seed=%d winner %d of 144" % (i_aa, seed, chosen - begin), flush=True)
+        assert vp.read_status(st) == 0
+        g = vp.schedule_to_host(out)
+        best = next(c for c in cands if c["family"] == chosen)
+        dst, nbytes, inst = np.zeros(N, np.int32), np.zeros(N, np.int64), np.zeros(N, np.int32)
+        dst[best["src"]], nbytes[best["src"]] = best["dst"], best["x"]
+        inst[best["src"]] = o.cluster_family(chosen)["id"]
+        assert g["family"][0] == chosen - begin, seed
+        assert np.array_equal(g["dst"][0], dst) and np.array_equal(g["bytes"][0], nbytes), seed
+        assert np.array_equal(g["inst"][0], inst), seed
+        # the whole schedule: every instance joins its lane's switches, and the demand is served exactly
+        served = np.zeros_like(D)
+        for k in range(g["K"]):
+            assert np.array_equal(np.sort(g["dst"][k]), rank), (seed, k)
+            assert np.array_equal(tab["src"][g["inst"][k]], slot), (seed, k)
+            assert np.array_equal(tab["dst"][g["inst"][k]], slot[g["dst"][k]]), (seed, k)
+            served[rank, g["dst"][k]] += g["bytes"][k]
+        assert np.array_equal(served, D), seed
+    assert past_the_last >= 4   # winners that the last, short chunk has no family for
