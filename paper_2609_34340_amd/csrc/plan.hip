@@ -1052,6 +1052,9 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
       ++half_step;
       fetch_out(dw);
       if (part == 0 && lane == 0) sh->triple[slot] = 0;   // both wavefronts have read it
+      // The next run's maximum must find the word cleared: a half-step's
+      // barrier lies between, or this one where there is none.
+      if (P.i_aa == 0) lds_barrier();
     }
     bool stale = S == 1;   // jf is older than del
     for (int sweep = 0; sweep < P.i_aa; ++sweep) {

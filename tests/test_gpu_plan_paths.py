@@ -127,7 +127,7 @@ def cut_catalog(vp, topo, begin, end):
 # A shape of 144 families (chunks of 64, 64 and 16) whose starts take two wavefronts each: the winner's chunk is not the
 # last one, so its run is made again.  One start without draws, so that the families' numbers in the cut catalog do not
 # matter, and the oracle's binding of the same shape of the whole catalog is the one to find.
-@pytest.mark.parametrize("i_aa", [8])
+@pytest.mark.parametrize("i_aa", [8, 0])
 def test_winner_in_an_earlier_chunk(vp, i_aa):
     topo = vpgen.Topology(43, 1, 3, 2, 2)
     o = oracle.Catalog(topo)
@@ -170,3 +170,18 @@ def test_winner_in_an_earlier_chunk(vp, i_aa):
             served[rank, g["dst"][k]] += g["bytes"][k]
         assert np.array_equal(served, D), seed
     assert past_the_last >= 4   # winners that the last, short chunk has no family for
+
+
+# Shapes of many families, two wavefronts per start, with and without sweeps: every slot starts one run after another
+# from the canonical binding, with no barrier of a half-step between them where there are no sweeps.
+@pytest.mark.parametrize("topo", [vpgen.Topology(43, 1, 3, 2, 2), vpgen.Topology(66, 1, 2, 2, 2),
+                                  vpgen.Topology(33, 1, 2, 3, 2)], ids=lambda t: "x".join(map(str, t.as_tuple()[:5])))
+@pytest.mark.parametrize("n_start,i_aa", [(1, 0), (4, 0), (1, 8), (4, 1)])
+def test_rounds_of_families(vp, topo, n_start, i_aa):
+    N, n = topo.n_ranks, topo.n_ranks // topo.n_nodes
+    rng = np.random.default_rng(N)
+    node = np.arange(N) // n
+    shift = (node[None] - node[:, None]) % topo.n_nodes
+    D = (rng.integers(0, 200, (N, N)) * ((shift == 0) | (shift == 5)) * UNIT).astype(np.int64)
+    np.fill_diagonal(D, 0)
+    check(vp, topo, D, n_start=n_start, i_aa=i_aa, k_target=64, k_max=12)
