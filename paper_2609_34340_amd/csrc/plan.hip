@@ -82,7 +82,7 @@ __device__ unsigned long long g_phase_stamps[4096 * 16];
 
 struct Shared {
   int64_t total, total_units;
-  int64_t tau;
+  int64_t Lmax;                // largest row or column sum in bytes, of a refused demand only
   int32_t capu[2];             // lane cap in units: PCIe-rate paths, NIC
   uint32_t Lmax_units;         // largest row or column sum
   int32_t err, huge;           // huge: some demand entry reaches 2^42 bytes
@@ -423,6 +423,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
   if (tid == 0) {
     sh->total = 0;
     sh->total_units = 0;
+    sh->Lmax = 0;
     sh->Lmax_units = 0;
     sh->err = 0;
     sh->huge = 0;
@@ -542,13 +543,14 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
   __syncthreads();
   // the quantum and the lane caps, in every wavefront
   int err = lane0(sh->err);
-  const int64_t Lmax = lane0((int64_t)sh->Lmax_units) * P.unit, total_units = lane0(sh->total_units);
-  int64_t tau;
+  const int64_t total_units = lane0(sh->total_units);
+  auto quantum = [&](int64_t Lmax) {
+    const int64_t den = L.bw_max * P.k_target, t = exact_div(Lmax + den - 1, den);
+    return t < 1 ? (int64_t)1 : t;
+  };
+  int64_t tau = quantum(lane0((int64_t)sh->Lmax_units) * P.unit);
   uint32_t cap_p = 1, cap_n = 1;   // units
   {
-    const int64_t den = L.bw_max * P.k_target;
-    tau = exact_div(Lmax + den - 1, den);
-    if (tau < 1) tau = 1;
     bool over = false;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
@@ -559,7 +561,19 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
       (c ? cap_n : cap_p) = (uint32_t)cu;
     }
     over |= sh->huge != 0 || sh->total >= (int64_t(1) << 42) || total_units >= (int64_t(1) << 28);
-    if (err == 0 && over) err = VP_ERR_UNSUPPORTED;
+    if (err == 0 && over) {
+      // the quantum goes out with the refusal too: the 32-bit sums may have
+      // wrapped, so row and column sums again in 64 bits
+      err = VP_ERR_UNSUPPORTED;
+      const int64_t* gD = P.D + b * NN;
+      for (int x = tid; x < 2 * N; x += kPlanThreads) {
+        int64_t sum = 0;
+        for (int y = 0; y < N; ++y) sum += x < N ? gD[(size_t)x * N + y] : gD[(size_t)y * N + (x - N)];
+        if (sum > 0) atomicMax((unsigned long long*)&sh->Lmax, (unsigned long long)sum);
+      }
+      __syncthreads();
+      tau = quantum(sh->Lmax);
+    }
   }
   err = lane0(err);
   cap_p = (uint32_t)lane0((int32_t)cap_p);

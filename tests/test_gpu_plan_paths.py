@@ -185,3 +185,28 @@ def test_rounds_of_families(vp, topo, n_start, i_aa):
     D = (rng.integers(0, 200, (N, N)) * ((shift == 0) | (shift == 5)) * UNIT).astype(np.int64)
     np.fill_diagonal(D, 0)
     check(vp, topo, D, n_start=n_start, i_aa=i_aa, k_target=64, k_max=12)
+
+
+# The quantum of a refused demand: of its true row and column sums, also where they do not fit the 32 bits (in units)
+# that the sums of an accepted demand fit in.
+@pytest.mark.parametrize("nodes", [1, 3, 33])
+@pytest.mark.parametrize("unit,entries,k_target", [
+    (16, {(0, 1): 1 << 40}, 16),                                      # 2^36 units
+    (1, {(0, 1): 3 << 40, (2, 1): 1 << 41}, 1),                       # a column of 2^42 bytes and more
+    (16, {(3, 1): 1 << 36, (3, 2): 1 << 35, (3, 5): 16}, 64),         # 2^32 units meet in a row
+    (4096, {(7, 0): 1 << 50, (6, 0): 4096}, 1000),                    # an entry past 2^42
+    (16, {(0, 1): 1 << 31, (2, 3): 1 << 31}, 4096)])                  # sums that fit, 2^28 units in all
+def test_quantum_of_a_refused_demand(vp, nodes, unit, entries, k_target):
+    topo = vpgen.Topology(nodes)
+    N = topo.n_ranks
+    D = np.zeros((N, N), np.int64)
+    for (i, j), v in entries.items():
+        D[N - 1 - i, N - 1 - j] = v
+    cat = vp.Catalog(topo)
+    cat.upload()
+    st = vp.new_status()
+    out = vp.plan(cat, torch.from_numpy(D).cuda(), vp.plan_params(N, unit, k_target=k_target), status=st)
+    torch.cuda.synchronize()
+    assert vp.read_status(st) == vp.UNSUPPORTED and int(out["K"]) == 0
+    den = topo.pcie_bytes_per_ns * k_target
+    assert int(out["tau"]) == -(-int(max(D.sum(0).max(), D.sum(1).max())) // den)
