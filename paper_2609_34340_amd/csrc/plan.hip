@@ -379,7 +379,13 @@ struct Order<2> {
 // per activation against 15.1 with four groups per lane, whose registers
 // spill; 320 ranks of four: 16.5 against 28), while at 256 ranks of two it
 // costs more (4.1 against 3.5 us).
-template <int g, int MG, bool RL, int S>
+// MS: more starts than run side by side, which then take turns on a slot: it
+// reads the family's lanes and credits once and keeps its best binding.  As
+// single runs on the path of many families, with a second run of the winner,
+// sixteen starts took 7.2 us per activation at 64 ranks, 11.6 at 256 and 28 at
+// 512; this way 3.9, 6.6 and 17.4.  (1,024 threads give every start its own
+// wavefront but 128 registers: 4.0, 9.6 and 31.)
+template <int g, int MG, bool RL, int S, bool MS>
 __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int g2 = g * g, RW = kResWords<g>;
@@ -818,16 +824,20 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
   // its destination), `ent` (out-lane descriptor), `dg` (destination group)
   // and `xv` (units); returns the binding score F (Eq. (8)) and, if need_x,
   // the largest lane volume on PCIe-rate and NIC paths.
-  struct Binding {
+  struct Bound {
     Order<g> sig[MG];
     int jf[MG][g];   // for g = 2 a mask, all ones for member 1
     __device__ int member(int r, int m) const { return g == 2 ? jf[r][m] & 1 : jf[r][m]; }
-    OutLanes o;
     uint32_t xv[MG][g];
-    uint32_t left[RL ? 1 : MG][g];   // D^rem in global memory: the residual of each lane's pair
+    uint32_t left[RL || MS ? 1 : MG][g];   // D^rem in global memory: the residual of each lane's pair
   };
-  auto run = [&](Binding& B, int lf, int kstar, int fbase, int start, uint64_t step_key, bool need_x, uint32_t& xp,
-                 uint32_t& xn) __attribute__((always_inline)) -> uint32_t {
+  struct Binding : Bound {
+    OutLanes o;
+  };
+  // MS, all_starts: the slot's starts one after another on the same lanes and
+  // credits; `start` becomes the one kept, its first best.
+  auto run = [&](Binding& B, int lf, int kstar, int fbase, int& start, uint64_t step_key, bool all_starts, bool need_x,
+                 uint32_t& xp, uint32_t& xn) __attribute__((always_inline)) -> uint32_t {
     uint32_t rec[MG][g];
     read_records(rec, lf);
     OutLanes& o = B.o;
@@ -892,28 +902,21 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         oword[r][m] = word_of(o.d[r][m]);
       }
     }
-    Order<g> del[MG];
-    if (start == 0) {
-#pragma unroll
-      for (int r = 0; r < MG; ++r) {
-        B.sig[r].identity();
-        del[r].identity();
-      }
-    } else {
-      draw(B.sig, del, step_key, fbase + lf, start);
-    }
     int32_t hs[HM][g][g2], hd[HM][g][g2];
-    if constexpr (kHold) {
+    auto hold = [&]() __attribute__((always_inline)) {
+      if constexpr (kHold) {
 #pragma unroll
-      for (int r = 0; r < MG; ++r)
+        for (int r = 0; r < MG; ++r)
 #pragma unroll
-        for (int m = 0; m < g; ++m)
+          for (int m = 0; m < g; ++m)
 #pragma unroll
-          for (int e = 0; e < g2; ++e) {
-            hs[r][m][e] = credit(raw[r][m][e], ocap[r][m], e / g == e % g && oself[r][m]);
-            hd[r][m][e] = credit(rin[r][m][e], icap[r][m], e / g == e % g && iself[r][m]);
-          }
-    }
+            for (int e = 0; e < g2; ++e) {
+              hs[r][m][e] = credit(raw[r][m][e], ocap[r][m], e / g == e % g && oself[r][m]);
+              hd[r][m][e] = credit(rin[r][m][e], icap[r][m], e / g == e % g && iself[r][m]);
+            }
+      }
+    };
+    if constexpr (MS) hold();
     // credit of out-lane (r, m) from source il to member jl, and of in-lane
     // (r, m) from member il to destination jl
     auto out_credit = [&](int r, int m, int il, int jl) {
@@ -922,263 +925,299 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     auto in_credit = [&](int r, int m, int il, int jl) {
       return credit(res[(sg[r][m] * (uint32_t)G + (uint32_t)ga[r]) * RW + il * g + jl], icap[r][m], il == jl && iself[r][m]);
     };
-    // Start 0: the canonical binding with the highest-credit triple put in;
-    // its lane's out- and in-list positions are protected (-1: none here).
-    int prot_o[MG], prot_i[MG];
-#pragma unroll
-    for (int r = 0; r < MG; ++r) prot_o[r] = prot_i[r] = -1;
-    auto bind_top = [&](int a, int m0, int il, int jl, int d, int mi) {
-#pragma unroll
-      for (int r = 0; r < MG; ++r) {
-        // members are still in order: the one to move is at its own position
-        const bool so = ga[r] == a && own[r], di = ga[r] == d && own[r];
-        prot_o[r] = so ? m0 : -1;
-        B.sig[r].swap_if(so, m0, il);
-        prot_i[r] = di ? mi : -1;
-        del[r].swap_if(di, mi, jl);
-      }
-    };
-    auto bind_pack = [&](uint32_t w) {
-      bind_top((int)(w & 511), (int)((w >> 18) & 3), (int)((w >> 20) & 3), (int)((w >> 22) & 3), (int)((w >> 9) & 511),
-               (int)((w >> 24) & 3));
-    };
-    auto top_here = [&]() {
-      return find_top(o, [&](int x) -> int32_t {
-        const int r = x / (g * g2), m = x / g2 % g, e = x % g2;
-        if constexpr (kHold) return hs[r][m][e];
-        else return out_credit(r, m, e / g, e % g);
-      });
-    };
-    if constexpr (S == 1) {
+    auto bind = [&](Bound& B, int start) __attribute__((always_inline)) -> uint32_t {
+      Order<g> del[MG];
       if (start == 0) {
-        const Triple T = top_here();
-        if (T.top != 0) bind_pack(read_lane(T.pack, __builtin_ctzll(__ballot(T.mine))));
-      }
-    } else {
-      if (start == 0) {
-        // the two wavefronts' triples meet in one word: credit, (lane, i, j)
-        // inverted (below 2^14), destination group, position there
-        const Triple T = top_here();
-        if (T.mine && T.top != 0)
-          atomicMax((unsigned long long*)&sh->triple[slot],
-                    (unsigned long long)T.top << 32 | (unsigned long long)(0x3FFF - T.key) << 16 |
-                        (unsigned long long)(((T.pack >> 9) & 511) << 2 | ((T.pack >> 24) & 3)));
-      }
-      lds_barrier();   // every wavefront comes here: runs are in step
-      if (start == 0) {
-        const uint64_t w = (uint64_t)lane0((int64_t)sh->triple[slot]);
-        if (w != 0) {
-          const uint32_t key = 0x3FFF - ((uint32_t)(w >> 16) & 0x3FFF), t = key / (uint32_t)g2, e = key % (uint32_t)g2;
-          int a = -1, m0 = 0;   // on the lane that owns it
 #pragma unroll
-          for (int r = 0; r < MG; ++r)
+        for (int r = 0; r < MG; ++r) {
+          B.sig[r].identity();
+          del[r].identity();
+        }
+      } else {
+        draw(B.sig, del, step_key, fbase + lf, start);
+      }
+      if constexpr (!MS) hold();   // the loads are under way while the orders are drawn
+      // Start 0: the canonical binding with the highest-credit triple put in;
+      // its lane's out- and in-list positions are protected (-1: none here).
+      int prot_o[MG], prot_i[MG];
 #pragma unroll
-            for (int m = 0; m < g; ++m)
-              if (own[r] && (uint32_t)(gn[r] * QG) + ((o.e[r][m] >> 8) & 31) == t) {
-                a = ga[r];
-                m0 = m;
-              }
-          bind_top(a, m0, (int)(e / g), (int)(e % g), (int)((w >> 2) & 0x3FFF), (int)(w & 3));
+      for (int r = 0; r < MG; ++r) prot_o[r] = prot_i[r] = -1;
+      auto bind_top = [&](int a, int m0, int il, int jl, int d, int mi) {
+#pragma unroll
+        for (int r = 0; r < MG; ++r) {
+          // members are still in order: the one to move is at its own position
+          const bool so = ga[r] == a && own[r], di = ga[r] == d && own[r];
+          prot_o[r] = so ? m0 : -1;
+          B.sig[r].swap_if(so, m0, il);
+          prot_i[r] = di ? mi : -1;
+          del[r].swap_if(di, mi, jl);
+        }
+      };
+      auto bind_pack = [&](uint32_t w) {
+        bind_top((int)(w & 511), (int)((w >> 18) & 3), (int)((w >> 20) & 3), (int)((w >> 22) & 3), (int)((w >> 9) & 511),
+                 (int)((w >> 24) & 3));
+      };
+      auto top_here = [&]() {
+        return find_top(o, [&](int x) -> int32_t {
+          const int r = x / (g * g2), m = x / g2 % g, e = x % g2;
+          if constexpr (kHold) return hs[r][m][e];
+          else return out_credit(r, m, e / g, e % g);
+        });
+      };
+      if constexpr (S == 1) {
+        if (start == 0) {
+          const Triple T = top_here();
+          if (T.top != 0) bind_pack(read_lane(T.pack, __builtin_ctzll(__ballot(T.mine))));
+        }
+      } else {
+        if (start == 0) {
+          // the two wavefronts' triples meet in one word: credit, (lane, i, j)
+          // inverted (below 2^14), destination group, position there
+          const Triple T = top_here();
+          if (T.mine && T.top != 0)
+            atomicMax((unsigned long long*)&sh->triple[slot],
+                      (unsigned long long)T.top << 32 | (unsigned long long)(0x3FFF - T.key) << 16 |
+                          (unsigned long long)(((T.pack >> 9) & 511) << 2 | ((T.pack >> 24) & 3)));
+        }
+        lds_barrier();   // every wavefront comes here: runs are in step
+        if (start == 0) {
+          const uint64_t w = (uint64_t)lane0((int64_t)sh->triple[slot]);
+          if (w != 0) {
+            const uint32_t key = 0x3FFF - ((uint32_t)(w >> 16) & 0x3FFF), t = key / (uint32_t)g2, e = key % (uint32_t)g2;
+            int a = -1, m0 = 0;   // on the lane that owns it
+#pragma unroll
+            for (int r = 0; r < MG; ++r)
+#pragma unroll
+              for (int m = 0; m < g; ++m)
+                if (own[r] && (uint32_t)(gn[r] * QG) + ((o.e[r][m] >> 8) & 31) == t) {
+                  a = ga[r];
+                  m0 = m;
+                }
+            bind_top(a, m0, (int)(e / g), (int)(e % g), (int)((w >> 2) & 0x3FFF), (int)(w & 3));
+          }
         }
       }
-    }
-    // Self-binding repair, per group in out-list order: trade destinations
-    // with the first other unprotected in-lane, else sources with the first
-    // other unprotected out-lane.
+      // Self-binding repair, per group in out-list order: trade destinations
+      // with the first other unprotected in-lane, else sources with the first
+      // other unprotected out-lane.
 #pragma unroll
-    for (int r = 0; r < MG; ++r)
+      for (int r = 0; r < MG; ++r)
 #pragma unroll
-      for (int m = 0; m < g; ++m) {
-        const int mi = pos_index(o.pos[r][m]);
-        if (oself[r][m] && B.sig[r].at(m) == del[r].at(mi)) {
-          int pi = -1, po = -1;
+        for (int m = 0; m < g; ++m) {
+          const int mi = pos_index(o.pos[r][m]);
+          if (oself[r][m] && B.sig[r].at(m) == del[r].at(mi)) {
+            int pi = -1, po = -1;
 #pragma unroll
-          for (int x = g - 1; x >= 0; --x) {
-            pi = x != mi && x != prot_i[r] ? x : pi;
-            po = x != m && x != prot_o[r] ? x : po;
+            for (int x = g - 1; x >= 0; --x) {
+              pi = x != mi && x != prot_i[r] ? x : pi;
+              po = x != m && x != prot_o[r] ? x : po;
+            }
+            del[r].swap_if(pi >= 0, mi, pi);
+            B.sig[r].swap_if(pi < 0 && po >= 0, m, po);
           }
-          del[r].swap_if(pi >= 0, mi, pi);
-          B.sig[r].swap_if(pi < 0 && po >= 0, m, po);
         }
-      }
-    // Alternating Algorithm: source half, then destination half.  A half that
-    // changes nothing, other than the very first, leaves a fixed point: the
-    // half before it made its own side optimal against this side, which has
-    // not moved.  Stopping there gives the same binding as stopping after a
-    // whole unchanged sweep.
-    auto pack = [&](const Order<g> (&a)[MG]) -> uint32_t {
-      if constexpr (g == 2 && MG == 1) return (uint32_t)a[0].p;
-      else return order_word(a);
-    };
-    // entry `i` of a row (or column) of credits, i a member or, for g = 2, its mask
-    auto pick = [&](const int32_t (&c)[g], int i) {
-      if constexpr (g == 2) {
-        return bit_select(i, c[1], c[0]);
-      } else {
-        int32_t v = c[0];
-#pragma unroll
-        for (int x = 1; x < g; ++x) v = bit_select(i == x ? -1 : 0, c[x], v);
-        return v;
-      }
-    };
-    // Member at the other side of a lane, from this lane's view of that side's
-    // orders `w`: a permute, or (S = 2) the words that publish() left in LDS.
-    auto fetch = [&](uint32_t from, int pos, uint32_t w, int side) {
-      const uint32_t at = MG == 1 ? from : from & 0xFFFF, shift = MG == 1 ? 0 : from >> 16;
-      uint32_t v;
-      if constexpr (S == 1) v = (uint32_t)__builtin_amdgcn_ds_bpermute((int)at, (int)w);
-      else v = *(const uint32_t*)((const char*)(xw + side * S * 64) + at);
-      if constexpr (g == 2) {   // a mask: all ones is member 1 (`pos` is one as well)
-        if constexpr (MG == 1) return (int)v ^ pos;
-        else return ((int)(v << (31 - shift)) >> 31) ^ pos;
-      } else {
-        if constexpr (MG > 1) v >>= shift;
-        return Order<g>::member(v, pos);
-      }
-    };
-    VP_STAMP(5);
-    // S = 2: leave the orders in LDS and learn whether any run has changed in
-    // this half-step (a run at its fixed point stays there).  The flags of
-    // four half-steps rotate: one is cleared two half-steps before it is used.
-    auto publish = [&](int side, uint32_t w, bool changed) {
-      xw[side * S * 64 + part * 64 + lane] = w;
-      if (changed && lane == 0) sh->changed[half_step & 3] = 1;
-      if (tid == 0) sh->changed[(half_step + 2) & 3] = 0;
-      lds_barrier();
-    };
-    auto any_changed = [&]() -> bool { return lane0(sh->changed[half_step++ & 3]) != 0; };
-    int il[MG][g];
-    auto fetch_out = [&](uint32_t w) {
-#pragma unroll
-      for (int r = 0; r < MG; ++r)
-#pragma unroll
-        for (int m = 0; m < g; ++m) B.jf[r][m] = fetch(oword[r][m], o.pos[r][m], w, 1);
-    };
-    auto fetch_in = [&](uint32_t w) {
-#pragma unroll
-      for (int r = 0; r < MG; ++r)
-#pragma unroll
-        for (int m = 0; m < g; ++m) il[r][m] = fetch(iword[r][m], ipos[r][m], w, 0);
-    };
-    uint32_t dw = pack(del);
-    if constexpr (S == 2) {
-      publish(1, dw, false);
-      ++half_step;
-      fetch_out(dw);
-      if (part == 0 && lane == 0) sh->triple[slot] = 0;   // both wavefronts have read it
-      // The next run's maximum must find the word cleared: a half-step's
-      // barrier lies between, or this one where there is none.
-      if (P.i_aa == 0) lds_barrier();
-    }
-    bool stale = S == 1;   // jf is older than del
-    for (int sweep = 0; sweep < P.i_aa; ++sweep) {
-      bool changed = false;
-      if constexpr (S == 1) {
-        fetch_out(dw);
-        stale = false;
-      }
-#pragma unroll
-      for (int r = 0; r < MG; ++r) {
-        int32_t h[g][g];
-#pragma unroll
-        for (int m = 0; m < g; ++m)
-#pragma unroll
-          for (int il = 0; il < g; ++il) {
-            if constexpr (kHold) {
-              int32_t row[g];
-#pragma unroll
-              for (int jj = 0; jj < g; ++jj) row[jj] = hs[r][m][il * g + jj];
-              h[m][il] = pick(row, B.jf[r][m]);
-            } else {
-              h[m][il] = out_credit(r, m, il, B.member(r, m));
-            }
-          }
-        changed |= B.sig[r].improve(h);
-      }
-      changed = __any(changed);
-      if constexpr (S == 1) {
-        if (sweep > 0 && !changed) break;
-        fetch_in(pack(B.sig));
-      } else {
-        const uint32_t sw = pack(B.sig);
-        publish(0, sw, changed);
-        fetch_in(sw);
-        if (!any_changed() && sweep > 0) break;
-      }
-      changed = false;
-#pragma unroll
-      for (int r = 0; r < MG; ++r) {
-        int32_t h[g][g];
-#pragma unroll
-        for (int m = 0; m < g; ++m)
-#pragma unroll
-          for (int jl = 0; jl < g; ++jl) {
-            if constexpr (kHold) {
-              int32_t col[g];
-#pragma unroll
-              for (int ii = 0; ii < g; ++ii) col[ii] = hd[r][m][ii * g + jl];
-              h[m][jl] = pick(col, il[r][m]);
-            } else {
-              h[m][jl] = in_credit(r, m, g == 2 ? il[r][m] & 1 : il[r][m], jl);
-            }
-          }
-        changed |= del[r].improve(h);
-      }
-      changed = __any(changed);
-      if constexpr (S == 1) {
-        if (!changed) break;
-        dw = pack(del);
-        stale = true;
-      } else {
-        dw = pack(del);
-        publish(1, dw, changed);
-        fetch_out(dw);
-        if (!any_changed()) break;
-      }
-    }
-    VP_STAMP(6);
-    if (stale) fetch_out(dw);
-    // in global memory the residuals that the winner lowers are asked for
-    // ahead of the comparison of the starts
-    if constexpr (!RL) {
-#pragma unroll
-      for (int r = 0; r < MG; ++r)
-#pragma unroll
-        for (int m = 0; m < g; ++m)
-          B.left[r][m] = res[((uint32_t)(ga[r] * G) + o.d[r][m]) * RW + (uint32_t)(B.sig[r].at(m) * g + B.member(r, m))];
-    }
-    uint32_t F = 0;
-    xp = xn = 0;
-#pragma unroll
-    for (int r = 0; r < MG; ++r)
-#pragma unroll
-      for (int m = 0; m < g; ++m) {
-        int32_t x;
-        if constexpr (kHold) {
-          int32_t row[g], col[g];
-#pragma unroll
-          for (int j2 = 0; j2 < g; ++j2) {
-#pragma unroll
-            for (int i2 = 0; i2 < g; ++i2) col[i2] = hs[r][m][i2 * g + j2];
-            if constexpr (g == 2) row[j2] = pick(col, B.sig[r].at_mask(m));
-            else row[j2] = pick(col, B.sig[r].at(m));
-          }
-          x = pick(row, B.jf[r][m]);
+      // Alternating Algorithm: source half, then destination half.  A half that
+      // changes nothing, other than the very first, leaves a fixed point: the
+      // half before it made its own side optimal against this side, which has
+      // not moved.  Stopping there gives the same binding as stopping after a
+      // whole unchanged sweep.
+      auto pack = [&](const Order<g> (&a)[MG]) -> uint32_t {
+        if constexpr (g == 2 && MG == 1) return (uint32_t)a[0].p;
+        else return order_word(a);
+      };
+      // entry `i` of a row (or column) of credits, i a member or, for g = 2, its mask
+      auto pick = [&](const int32_t (&c)[g], int i) {
+        if constexpr (g == 2) {
+          return bit_select(i, c[1], c[0]);
         } else {
-          x = out_credit(r, m, B.sig[r].at(m), B.member(r, m));
+          int32_t v = c[0];
+#pragma unroll
+          for (int x = 1; x < g; ++x) v = bit_select(i == x ? -1 : 0, c[x], v);
+          return v;
         }
-        const uint32_t xu = (uint32_t)max(x, 0);   // a self pair serves nothing
-        B.xv[r][m] = xu;
-        F += xu;
-        xn = max(xn, xu & (uint32_t)o.nic(r, m));
-        xp = max(xp, xu & ~(uint32_t)o.nic(r, m));
+      };
+      // Member at the other side of a lane, from this lane's view of that side's
+      // orders `w`: a permute, or (S = 2) the words that publish() left in LDS.
+      auto fetch = [&](uint32_t from, int pos, uint32_t w, int side) {
+        const uint32_t at = MG == 1 ? from : from & 0xFFFF, shift = MG == 1 ? 0 : from >> 16;
+        uint32_t v;
+        if constexpr (S == 1) v = (uint32_t)__builtin_amdgcn_ds_bpermute((int)at, (int)w);
+        else v = *(const uint32_t*)((const char*)(xw + side * S * 64) + at);
+        if constexpr (g == 2) {   // a mask: all ones is member 1 (`pos` is one as well)
+          if constexpr (MG == 1) return (int)v ^ pos;
+          else return ((int)(v << (31 - shift)) >> 31) ^ pos;
+        } else {
+          if constexpr (MG > 1) v >>= shift;
+          return Order<g>::member(v, pos);
+        }
+      };
+      VP_STAMP(5);
+      // S = 2: leave the orders in LDS and learn whether any run has changed in
+      // this half-step (a run at its fixed point stays there).  The flags of
+      // four half-steps rotate: one is cleared two half-steps before it is used.
+      auto publish = [&](int side, uint32_t w, bool changed) {
+        xw[side * S * 64 + part * 64 + lane] = w;
+        if (changed && lane == 0) sh->changed[half_step & 3] = 1;
+        if (tid == 0) sh->changed[(half_step + 2) & 3] = 0;
+        lds_barrier();
+      };
+      auto any_changed = [&]() -> bool { return lane0(sh->changed[half_step++ & 3]) != 0; };
+      int il[MG][g];
+      auto fetch_out = [&](uint32_t w) {
+#pragma unroll
+        for (int r = 0; r < MG; ++r)
+#pragma unroll
+          for (int m = 0; m < g; ++m) B.jf[r][m] = fetch(oword[r][m], o.pos[r][m], w, 1);
+      };
+      auto fetch_in = [&](uint32_t w) {
+#pragma unroll
+        for (int r = 0; r < MG; ++r)
+#pragma unroll
+          for (int m = 0; m < g; ++m) il[r][m] = fetch(iword[r][m], ipos[r][m], w, 0);
+      };
+      uint32_t dw = pack(del);
+      if constexpr (S == 2) {
+        publish(1, dw, false);
+        ++half_step;
+        fetch_out(dw);
+        if (part == 0 && lane == 0) sh->triple[slot] = 0;   // both wavefronts have read it
+        // The next run's maximum must find the word cleared: a half-step's
+        // barrier lies between, or this one where there is none.
+        if (P.i_aa == 0) lds_barrier();
       }
-    F = wave_reduce<OpAdd>(F);
-    if (need_x) {   // the lane maxima only serve comparisons between families
-      xp = wave_reduce<OpMax>(xp);
-      xn = wave_reduce<OpMax>(xn);
+      bool stale = S == 1;   // jf is older than del
+      for (int sweep = 0; sweep < P.i_aa; ++sweep) {
+        bool changed = false;
+        if constexpr (S == 1) {
+          fetch_out(dw);
+          stale = false;
+        }
+#pragma unroll
+        for (int r = 0; r < MG; ++r) {
+          int32_t h[g][g];
+#pragma unroll
+          for (int m = 0; m < g; ++m)
+#pragma unroll
+            for (int il = 0; il < g; ++il) {
+              if constexpr (kHold) {
+                int32_t row[g];
+#pragma unroll
+                for (int jj = 0; jj < g; ++jj) row[jj] = hs[r][m][il * g + jj];
+                h[m][il] = pick(row, B.jf[r][m]);
+              } else {
+                h[m][il] = out_credit(r, m, il, B.member(r, m));
+              }
+            }
+          changed |= B.sig[r].improve(h);
+        }
+        changed = __any(changed);
+        if constexpr (S == 1) {
+          if (sweep > 0 && !changed) break;
+          fetch_in(pack(B.sig));
+        } else {
+          const uint32_t sw = pack(B.sig);
+          publish(0, sw, changed);
+          fetch_in(sw);
+          if (!any_changed() && sweep > 0) break;
+        }
+        changed = false;
+#pragma unroll
+        for (int r = 0; r < MG; ++r) {
+          int32_t h[g][g];
+#pragma unroll
+          for (int m = 0; m < g; ++m)
+#pragma unroll
+            for (int jl = 0; jl < g; ++jl) {
+              if constexpr (kHold) {
+                int32_t col[g];
+#pragma unroll
+                for (int ii = 0; ii < g; ++ii) col[ii] = hd[r][m][ii * g + jl];
+                h[m][jl] = pick(col, il[r][m]);
+              } else {
+                h[m][jl] = in_credit(r, m, g == 2 ? il[r][m] & 1 : il[r][m], jl);
+              }
+            }
+          changed |= del[r].improve(h);
+        }
+        changed = __any(changed);
+        if constexpr (S == 1) {
+          if (!changed) break;
+          dw = pack(del);
+          stale = true;
+        } else {
+          dw = pack(del);
+          publish(1, dw, changed);
+          fetch_out(dw);
+          if (!any_changed()) break;
+        }
+      }
+      VP_STAMP(6);
+      if (stale) fetch_out(dw);
+      // in global memory the residuals that the winner lowers are asked for
+      // ahead of the comparison of the starts
+      if constexpr (!RL && !MS) {
+#pragma unroll
+        for (int r = 0; r < MG; ++r)
+#pragma unroll
+          for (int m = 0; m < g; ++m)
+            B.left[r][m] = res[((uint32_t)(ga[r] * G) + o.d[r][m]) * RW + (uint32_t)(B.sig[r].at(m) * g + B.member(r, m))];
+      }
+      uint32_t F = 0;
+      xp = xn = 0;
+#pragma unroll
+      for (int r = 0; r < MG; ++r)
+#pragma unroll
+        for (int m = 0; m < g; ++m) {
+          int32_t x;
+          if constexpr (kHold) {
+            int32_t row[g], col[g];
+#pragma unroll
+            for (int j2 = 0; j2 < g; ++j2) {
+#pragma unroll
+              for (int i2 = 0; i2 < g; ++i2) col[i2] = hs[r][m][i2 * g + j2];
+              if constexpr (g == 2) row[j2] = pick(col, B.sig[r].at_mask(m));
+              else row[j2] = pick(col, B.sig[r].at(m));
+            }
+            x = pick(row, B.jf[r][m]);
+          } else {
+            x = out_credit(r, m, B.sig[r].at(m), B.member(r, m));
+          }
+          const uint32_t xu = (uint32_t)max(x, 0);   // a self pair serves nothing
+          B.xv[r][m] = xu;
+          F += xu;
+          xn = max(xn, xu & (uint32_t)o.nic(r, m));
+          xp = max(xp, xu & ~(uint32_t)o.nic(r, m));
+        }
+      F = wave_reduce<OpAdd>(F);
+      if (need_x) {   // the lane maxima only serve comparisons between families
+        xp = wave_reduce<OpMax>(xp);
+        xn = wave_reduce<OpMax>(xn);
+      }
+      return F;
+    };
+    if constexpr (!MS) {
+      return bind(B, start);
+    } else {
+      uint32_t top = 0;
+      const int first = start;
+      for (int s0 = first - slot;; s0 += kSlots) {
+        const int s = all_starts ? min(s0 + slot, NS - 1) : first;
+        Bound C;
+        uint32_t F = bind(C, s);
+        if (S == 2 && all_starts) {   // the score of both wavefronts
+          if (lane == 0) prF[s * S + part] = (int32_t)F;
+          lds_barrier();
+          const int2 f2 = ((const int2*)prF)[s];
+          F = (uint32_t)lane0(f2.x + f2.y);
+        }
+        if (s0 == first - slot || F > top) {
+          (Bound&)B = C;
+          top = F;
+          start = s;
+        }
+        if (!all_starts || (S == 1 ? s0 + kSlots + slot : s0 + kSlots) >= NS) return top;
+      }
     }
-    return F;
   };
   // Subtract X(E*) from D^rem and the aggregates and leave the lanes for the
   // writers.
@@ -1193,7 +1232,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         out[ga[r] * g + il] = make_uint2((d * g + (uint32_t)jl) | (e & 0x1F00) << 8, x);
         uint32_t* dp = res + ((uint32_t)(ga[r] * G) + d) * RW + (uint32_t)(il * g + jl);
         if constexpr (RL) atomicSub(dp, x);
-        else if (x != 0) *dp = B.left[r][m] - x;
+        else if (x != 0) *dp = (MS ? *dp : B.left[r][m]) - x;
         // the lane's node block: its own node's, or the shifted one
         atomicSub(&agg[gq[r] * Q * kS + (int)(e & 7) * kS + (B.o.nic(r, m) & kstar)], (int32_t)x);
       }
@@ -1365,21 +1404,23 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
     uint32_t best_F;
     // (The probability only places the code.  As all but certain it took a
     // further 5 % off 256 ranks, but put 10 % on shapes of many families.)
-    const bool one_family = (key & 0x1000) == 0 && NS <= kSlots;
+    const bool one_family = (key & 0x1000) == 0 && (MS || NS <= kSlots);
     if (MG > 1 ? __builtin_expect(one_family, 1) : __builtin_expect_with_probability(one_family, 1, 0.6)) {
-      // one family, one start per wavefront: the first start with the highest
-      // score wins, no utility to compare
+      // one family: the first start with the highest score wins, no utility
+      // to compare
       const int lf = (int)(key & 0xFFF);
       Binding B;
       uint32_t xp, xn;
-      if constexpr (S == 1) {
-        if (slot < NS) {
-          const uint32_t F = run(B, lf, kstar, fbase, slot, step_key, false, xp, xn);
-          if (lane == 0) atomicMax(&sh->top[K & 1], F << 4 | (uint32_t)(15 - slot));   // F < 2^28
+      // a slot without a start: with two wavefronts per start it repeats the
+      // last one, so that the wavefronts stay in step
+      int start = S == 1 ? slot : min(slot, NS - 1);
+      if (MS || S == 2 || slot < NS) {
+        const uint32_t F = run(B, lf, kstar, fbase, start, step_key, MS, false, xp, xn);
+        if constexpr (S == 1) {
+          if (lane == 0) atomicMax(&sh->top[K & 1], F << 4 | (uint32_t)(15 - start));   // F < 2^28
+        } else if constexpr (!MS) {
+          if (lane == 0 && slot < NS) prF[slot * S + part] = (int32_t)F;
         }
-      } else {   // a slot without a start repeats the last one: the wavefronts stay in step
-        const uint32_t F = run(B, lf, kstar, fbase, min(slot, NS - 1), step_key, false, xp, xn);
-        if (lane == 0 && slot < NS) prF[slot * S + part] = (int32_t)F;
       }
       between();
       VP_STAMP(7);
@@ -1391,13 +1432,18 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         best_F = top >> 4;
         best = 15 - (int)(top & 15);
       } else {
-        const int2 f2 = ((const int2*)prF)[min(lane & (kSlots - 1), NS - 1)];
+        constexpr int kRow = MS ? kMaxStarts : kSlots;
+        const int2 f2 = ((const int2*)prF)[min(lane & (kRow - 1), NS - 1)];
         const uint32_t f = (uint32_t)(f2.x + f2.y);
-        uint32_t m = OpMax::f(f, row_ror<2>(f));   // the four slots repeat along the row
+        // the starts repeat along the rows of sixteen lanes
+        uint32_t m = MS ? OpMax::f(f, row_ror<8>(f)) : f;
+        if constexpr (MS) m = OpMax::f(m, row_ror<4>(m));
+        m = OpMax::f(m, row_ror<2>(m));
         m = OpMax::f(m, row_ror<1>(m));
         best_F = (uint32_t)lane0((int32_t)m);
         best = __builtin_ctzll(__ballot(f == best_F));
       }
+      if constexpr (MS) best &= kSlots - 1;   // its slot
       VP_STAMP(9);
       if (best_F != 0 && slot == best) apply(B, kstar);
       lf_prev = lf;
@@ -1419,11 +1465,12 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
         // past the chunk's last job a slot repeats it, so that the wavefronts stay in step; the winner's job counts
         // in its own chunk, which may be longer than the last one
         if (S == 2 && !redo) job = min(job, nc * NS - 1);
-        const int cj = job / NS, start = job - cj * NS;
+        const int cj = job / NS;
+        int start = job - cj * NS;
         Binding B;
         if (S == 2 || runs) {
           uint32_t xp, xn;
-          const uint32_t F = run(B, lb + (redo ? best_chunk : c0) + cj, kstar, fbase, start, step_key, true, xp, xn);
+          const uint32_t F = run(B, lb + (redo ? best_chunk : c0) + cj, kstar, fbase, start, step_key, false, true, xp, xn);
           if (lane == 0 && !redo && runs) {
             prF[job * S + part] = (int32_t)F;
             prxp[job * S + part] = (int32_t)xp;
@@ -1552,9 +1599,9 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-template <int g, int MG, bool RL, int S>
-vp_status launch_t(const PlanArgs& P, size_t lds, hipStream_t st) {
-  auto kern = plan_kernel<g, MG, RL, S>;
+template <int g, int MG, bool RL, int S, bool MS>
+vp_status launch_s(const PlanArgs& P, size_t lds, hipStream_t st) {
+  auto kern = plan_kernel<g, MG, RL, S, MS>;
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
       hipSuccess)
     return set_error(VP_ERR_HIP, "cannot raise the planner's LDS limit");
@@ -1563,13 +1610,29 @@ vp_status launch_t(const PlanArgs& P, size_t lds, hipStream_t st) {
   return VP_OK;
 }
 
+template <int g, int MG, bool RL, int S>
+vp_status launch_t(const PlanArgs& P, size_t lds, hipStream_t st) {
+  if (P.n_start > kPlanWaves / S) return launch_s<g, MG, RL, S, true>(P, lds, st);
+  return launch_s<g, MG, RL, S, false>(P, lds, st);
+}
+
+// Wavefronts per (family, start) run (see plan_kernel).  Quads of 65 to 128
+// groups with more starts than fit two wavefronts each go back to one: 320
+// ranks, 8 and 16 starts 26.7 and 47 us per activation against 30.3 and 56.
+// Triples do not (384 ranks 21 against 13 us at 8 starts), nor more groups.
+int run_waves(int g, int G, int n_start) {
+  if (G <= (g == 2 ? 128 : 64)) return 1;
+  return g == 4 && G <= 128 && n_start > kPlanWaves / 2 ? 1 : 2;
+}
+
 template <int g>
 vp_status launch_g(const PlanArgs& P, size_t lds, hipStream_t st, bool res_lds) {
   const int G = P.L.G;
   if (G <= 64) return res_lds ? launch_t<g, 1, true, 1>(P, lds, st) : launch_t<g, 1, false, 1>(P, lds, st);
-  if constexpr (g == 2) {
-    if (G <= 128) return res_lds ? launch_t<g, 2, true, 1>(P, lds, st) : launch_t<g, 2, false, 1>(P, lds, st);
-  } else {
+  if (G <= 128 && run_waves(g, G, P.n_start) == 1) {
+    if constexpr (g != 3) return res_lds ? launch_t<g, 2, true, 1>(P, lds, st) : launch_t<g, 2, false, 1>(P, lds, st);
+  }
+  if constexpr (g != 2) {
     if (G <= 128) return res_lds ? launch_t<g, 1, true, 2>(P, lds, st) : launch_t<g, 1, false, 2>(P, lds, st);
   }
   if (G <= 256) return launch_t<g, 2, false, 2>(P, lds, st);
@@ -1708,7 +1771,7 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   };
   take(&P.o_agg, (size_t)L.kS * (L.Q * L.Q + 1) * 4);
   take(&P.o_rb, (size_t)(L.nS + 1) * 8);
-  const int parts = L.G <= (g == 2 ? 128 : 64) ? 1 : 2;   // wavefronts per run
+  const int parts = run_waves(g, L.G, NS);
   take(&P.o_pr, (size_t)P.FC * NS * parts * 12);
   take(&P.o_xw, parts == 1 ? 0 : (size_t)kPlanWaves / 2 * 256 * 4);
   take(&P.o_out, (size_t)N * 8);

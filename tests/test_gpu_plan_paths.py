@@ -110,6 +110,19 @@ def test_rounds_of_starts(vp, topo, n_start):
     check(vp, topo, D, n_start=n_start, i_aa=[8, 0, 1, 2][n_start % 4], seed=n_start)
 
 
+# more starts than run side by side, on every kernel that takes them in turn: groups per lane, wavefronts per start, D^rem
+# in LDS and not
+@pytest.mark.parametrize("topo", [vpgen.Topology(2), vpgen.Topology(17), vpgen.Topology(32), vpgen.Topology(33),
+                                  vpgen.Topology(65), vpgen.Topology(2, 1, 3, 3), vpgen.Topology(21, 1, 3, 3),
+                                  vpgen.Topology(22, 1, 3, 3), vpgen.Topology(43, 1, 3, 3), vpgen.Topology(86, 1, 3, 3),
+                                  vpgen.Topology(2, 1, 2, 4), vpgen.Topology(32, 1, 2, 4), vpgen.Topology(33, 1, 2, 4),
+                                  vpgen.Topology(65, 1, 2, 4)], ids=lambda t: "x".join(map(str, t.as_tuple()[:4])))
+@pytest.mark.parametrize("n_start,i_aa", [(5, 8), (8, 0), (9, 8), (16, 2)])
+def test_starts_in_turn(vp, topo, n_start, i_aa):
+    rng = np.random.default_rng(topo.n_ranks + n_start)
+    check(vp, topo, sparse_demand(rng, topo.n_ranks, 2.0, 8), n_start=n_start, i_aa=i_aa, seed=n_start)
+
+
 def cut_catalog(vp, topo, begin, end):
     """The catalog of `topo` with its shift-0 part cut to the families begin ... end - 1 (vp_catalog_load takes any
     subset): magic and topology (48 bytes), family counts of both parts and lanes per node (12), one byte per lane,
