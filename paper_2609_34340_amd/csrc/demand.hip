@@ -452,11 +452,17 @@ __global__ void __launch_bounds__(TH) demand_finish(DemandArgs a) {
 // launch between them.  The sorted row's wavefronts rank their ids, so their
 // counts are the row's; the others count by LDS atomics.  Measured, two passes
 // against one launch (graph replays): 768 ids 7.4 -> 4.0 us (one row and 64
-// alike), 256 rows of 2,048 ids 8.7 -> 5.6, of 4,096 ids 10.0 -> 8.9, 8 rows of
-// 4,096 ids 7.8 -> 7.3.  The gain ends there: beyond, one workgroup issues all
-// of a row's scattered stores (32,768 ids 11 us in two passes, 50 in one).
+// alike), 256 rows of 2,048 ids 8.7 -> 5.6, one row of 4,096 ids and 8, 256 or
+// 1,024 experts 7.5 -> 6.5, 9.0 -> 8.7 and 14.0 -> 10.0 (64 rows alike).  The
+// gain ends there: beyond, one workgroup issues all of a row's scattered stores
+// (32,768 ids 11 us in two passes, 50 in one).
+// The sorted row takes its demand from the expert offsets that it needs anyway.
+// The other rows add up each destination's experts, and scan too from more than
+// kScanLocal of them on: 8 destinations of 16 experts 2.68 us added, 2.74
+// scanned, of 32 3.34 and 2.90, of 128 7.6 and 3.5.
 constexpr int kSmallThreads = 512;
 constexpr int kSmallExperts = 1024;
+constexpr int kScanLocal = 16;
 
 template <int kPT>
 __global__ void __launch_bounds__(kSmallThreads) demand_small(DemandArgs a) {
@@ -504,15 +510,22 @@ __global__ void __launch_bounds__(kSmallThreads) demand_small(DemandArgs a) {
   }
   __syncthreads();
   const int eloc = E / a.N, self = a.first_rank + r;
+  int64_t* row = a.demand + (size_t)r * a.N;
+  if (!sorting && eloc <= kScanLocal) {
+    for (int j = tid; j < a.N; j += kSmallThreads) {
+      int64_t c = 0;
+      for (int e = j * eloc; e < (j + 1) * eloc; ++e) c += tot[e];
+      row[j] = j == self ? 0 : c * a.unit;
+    }
+    return;
+  }
+  const int32_t total = block_excl_scan<kSmallThreads>(tot, E, wtot);
   for (int j = tid; j < a.N; j += kSmallThreads) {
-    int64_t c = 0;
-    for (int e = j * eloc; e < (j + 1) * eloc; ++e) c += tot[e];
-    a.demand[(size_t)r * a.N + j] = j == self ? 0 : c * a.unit;
+    const int32_t lo = tot[j * eloc], hi = j + 1 < a.N ? tot[(j + 1) * eloc] : total;
+    row[j] = j == self ? 0 : (int64_t)(hi - lo) * a.unit;
+    if (sorting) a.dest_off[j] = lo;
   }
   if (!sorting) return;
-  __syncthreads();
-  const int32_t total = block_excl_scan<kSmallThreads>(tot, E, wtot);
-  for (int j = tid; j < a.N; j += kSmallThreads) a.dest_off[j] = tot[j * eloc];
   if (tid == 0) a.dest_off[a.N] = total;
   int at[kPT];
 #pragma unroll

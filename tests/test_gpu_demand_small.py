@@ -54,3 +54,24 @@ def test_bad_id_is_reported(vp, T, k, E, bad):
         torch.cuda.synchronize()
         assert vp.read_status(out["status"]) == vp.INVALID_ARGUMENT
         assert int(out["counts"].sum()) == 2 * T * k - 1
+
+
+# a row's demand from its experts' sums or from their offsets: destinations of one expert to all of them
+@pytest.mark.parametrize("E,N", [(1, 1), (1024, 1), (1024, 8), (136, 8), (128, 8), (120, 8), (1020, 60), (1024, 64),
+                                 (1024, 1024)])
+@pytest.mark.parametrize("T,k", [(1, 1), (77, 8), (4096, 1)])
+def test_demand_row_of_many_experts(vp, E, N, T, k):
+    rng = np.random.default_rng(E + N + T)
+    R = min(N, 3)
+    ids = rng.integers(0, E, (R, T, k)).astype(np.int32)
+    for sort_row in (-1, R - 1):
+        out = vp.demand(torch.from_numpy(ids).cuda(), N, E, 4112, first_rank=N - R, sort_row=sort_row)
+        torch.cuda.synchronize()
+        assert vp.read_status(out["status"]) == 0
+        for r in range(R):
+            ref = oracle.demand(ids[r], N, E, N - R + r, 4112)
+            assert np.array_equal(out["demand"][r].cpu().numpy(), ref["row"]), r
+            assert np.array_equal(out["counts"][r].cpu().numpy(), ref["counts"]), r
+        if sort_row >= 0:
+            assert np.array_equal(out["sorted_tok"].cpu().numpy()[:T * k], ref["sorted_tok"])
+            assert np.array_equal(out["dest_off"].cpu().numpy(), ref["dest_off"])
