@@ -291,13 +291,15 @@ size_t vp_plan_workspace(const vp_catalog* cat, const vp_plan_params* p);
  * (more than 4095 shapes of either kind, 255 node shifts, 256 node-local
  * instances, 512 rank groups, 8 switches per node or 4 GPUs per switch, or a
  * pattern with more intra-node lane classes or NIC lanes than its term
- * tables hold), and when the planner's
- * per-catalog state (shape terms, family lane maps, node aggregates) plus one
- * family's working set does not fit in one workgroup's LDS (160 KiB on gfx950):
- * two-socket nodes of two switches of three GPUs with cross-socket peer to
- * peer (2,744 families over 2,185 shapes from two nodes on) are the smallest
- * such catalogs met.  Larger catalogs need a planner that keeps those tables
- * in HBM. */
+ * tables hold), and when the catalog's size measure exceeds one workgroup's
+ * LDS (163,840 bytes on gfx950).  The measure is a limit of the library, above
+ * what the kernel itself lays out: per pattern 12 bytes and 2 for each of its
+ * slot pairs (the most of any pattern, up to a multiple of 8), per family 2 for
+ * each lane of a node, 24 per set of NIC lanes, 2 per NIC-carrying pattern, and
+ * a part that follows from ranks, groups, node shifts and starts.  Two-socket
+ * nodes of two switches of three GPUs with cross-socket peer to peer (2,744
+ * families over 2,185 shapes from two nodes on) are the smallest such catalogs
+ * met. */
 vp_status vp_plan(const vp_catalog* cat, const int64_t* demand, const vp_plan_params* p,
                   int32_t* K, int32_t* family, int32_t* dst, int32_t* inst, int64_t* bytes,
                   int64_t* send_off, int64_t* stream_off, int32_t* recv_src, int64_t* tau,

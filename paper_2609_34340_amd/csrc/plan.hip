@@ -1677,10 +1677,34 @@ vp_status static_residual(int32_t n_ranks, void** out) {
   return VP_OK;
 }
 
+namespace {
+
+// The library's limit on catalogs, in bytes to be held against one workgroup's
+// LDS: a measure of patterns, families, NIC-lane sets, ranks and starts, fixed
+// so that the catalogs taken do not change with the kernel's layout.  What the
+// kernel lays out (launch_plan) stays below it: of one pattern 2 Q g + 22 bytes
+// at most against 2 Q g + 28 here, its only family included.
+size_t catalog_measure(const DevCatalogLayout& L, int n_start) {
+  const size_t pairs = (size_t)((L.TS + 7) & ~7);   // slot pairs of a pattern
+  const size_t patterns = (size_t)(L.J0 + L.J1), families = (size_t)(L.F0 + L.F1);
+  const size_t N = (size_t)L.N, starts = (size_t)n_start;
+  const size_t lane_groups = L.G <= 64 ? 64 : L.G <= 128 ? 128 : L.G <= 256 ? 256 : 512;
+  size_t sum = 0;
+  for (size_t x : {112 + 35 * lane_groups * (size_t)L.g, (size_t)((L.nn + 3) | 1) * (size_t)(L.Q * L.Q + 1) * 4,
+                   patterns * pairs * 2, patterns * 8, patterns * 4, families * (size_t)(L.Q * L.g) * 2,
+                   (size_t)L.nS * kMaxRTerms * 2, (size_t)L.nS * 8, (size_t)L.J1 * 2, starts * 24,
+                   2 * align_up(N * 2, 16), 3 * align_up(N, 16), 2 * N * (size_t)((L.g * L.g) | 1) * 4,
+                   2 * align_up(starts * N, 16), (size_t)16, starts * (size_t)L.G * 2})
+    sum += align_up(x, 16);
+  return sum;
+}
+
+}  // namespace
+
 vp_status launch_plan(const PlanLaunch& a, void* stream) {
   const vp_catalog& c = *a.cat;
   const DevCatalogLayout& L = c.lay;
-  const int N = L.N, g = L.g, g2 = g * g, NS = a.p.n_start, NP = L.J0 + L.J1, FL = L.F0 + L.F1;
+  const int N = L.N, g = L.g, NS = a.p.n_start;
   const int QG = L.Q * g;
   if (L.J0 > 4095 || L.J1 > 4095 || L.nn > 255) return set_error(VP_ERR_UNSUPPORTED, "catalog too large");
   if (QG > kMaxQG || L.Q > 8 || g > 4) return set_error(VP_ERR_UNSUPPORTED, "too many lanes per node");
@@ -1748,21 +1772,8 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   size_t budget = 0;
   const vp_status ds = device_lds(&dev, &budget);
   if (ds != VP_OK) return ds;
-  // Catalogs the planner takes: the library's stated limit, the tables and
-  // one family's whole working set (lists, credits, residuals and every
-  // start's bindings) within one workgroup's LDS.  This kernel needs less.
-  {
-    const int TS8 = (L.TS + 7) & ~7, mg = L.G <= 64 ? 1 : L.G <= 128 ? 2 : L.G <= 256 ? 4 : 8;
-    const size_t n = (size_t)64 * mg * g;
-    size_t need = align_up(112 + 35 * n, 16);
-    for (size_t x : {(size_t)((L.nn + 3) | 1) * (L.Q * L.Q + 1) * 4, (size_t)NP * TS8 * 2, (size_t)NP * 8,
-                     (size_t)FL * QG * 2, (size_t)L.nS * kMaxRTerms * 2, (size_t)L.J1 * 2, (size_t)L.nS * 8,
-                     (size_t)NP * 4, (size_t)NS * 24, 2 * align_up((size_t)N * 2, 16), 3 * align_up((size_t)N, 16),
-                     2 * (size_t)N * (g2 | 1) * 4, 2 * align_up((size_t)NS * N, 16), (size_t)16,
-                     (size_t)NS * L.G * 2})
-      need += align_up(x, 16);
-    if (need > budget) return set_error(VP_ERR_UNSUPPORTED, "plan state does not fit in LDS");
-  }
+  if (catalog_measure(L, NS) > budget)
+    return set_error(VP_ERR_UNSUPPORTED, "catalog beyond the planner's limit (its size measure exceeds one workgroup's LDS)");
   P.FC = std::min(L.hmax, kFamChunk);
   size_t o = align_up(sizeof(Shared), 16);
   auto take = [&](int32_t* field, size_t bytes) {
