@@ -83,7 +83,6 @@ __device__ unsigned long long g_phase_stamps[4096 * 16];
 struct Shared {
   int64_t total, total_units;
   int64_t Lmax;                // largest row or column sum in bytes, of a refused demand only
-  int32_t capu[2];             // lane cap in units: PCIe-rate paths, NIC
   uint32_t Lmax_units;         // largest row or column sum
   int32_t err, huge;           // huge: some demand entry reaches 2^42 bytes
   // Argmaxes of even and odd iterations: of the shapes, score << 33 |

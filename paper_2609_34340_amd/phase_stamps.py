@@ -73,8 +73,7 @@ def main(configs):
         per_iter = float(np.mean(nxt - A[:, 0]))
         print("C%d %s: N=%d, plan %.1f us (stamped copy), K=%d, %.0f cycles per iteration" % (
             c, w.name, N, e0.elapsed_time(e1) * 1e3, K, per_iter), flush=True)
-        order = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11]
-        cols = [A[:, b] - A[:, a] for a, b in zip(order, order[1:])] + [nxt - A[:, 11]]
+        cols = [A[:, i + 1] - A[:, i] for i in range(11)] + [nxt - A[:, 11]]
         for name, d in zip(PHASES, cols):
             print("   %-34s %7.0f cycles  %5.1f %%" % (name, np.mean(d), 100 * np.mean(d) / per_iter), flush=True)
 
