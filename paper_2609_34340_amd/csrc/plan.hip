@@ -83,7 +83,10 @@ __device__ unsigned long long g_phase_stamps[4096 * 16];
 struct Shared {
   int64_t total, total_units;
   int64_t Lmax;                // largest row or column sum in bytes, of a refused demand only
-  uint32_t Lmax_units;         // largest row or column sum
+  // Aligned only for the code that the compiler then makes: with this and all
+  // that follows 8 bytes lower an activation takes 2.24 us for 2.20 at 8 ranks
+  // and 3.79 for 3.59 at 16 with cross-socket paths (other scalars spilled).
+  alignas(16) uint32_t Lmax_units;   // largest row or column sum
   int32_t err, huge;           // huge: some demand entry reaches 2^42 bytes
   // Argmaxes of even and odd iterations: of the shapes, score << 33 |
   // (2^20 - 1 - shape code) << 13 | payload, with code = shift << 12 |
