@@ -1257,7 +1257,10 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(PlanArgs P) {
       // activation's shift
       if (__builtin_expect(P.held, 1)) {
         if (kprev > 0) {
-          const int u0 = kprev - k0;   // an idle lane's sums are not used
+          // SPT is as many as the loop goes through, so that a lane takes its
+          // own shifts only: a copy of the next lane's would win a tie against
+          // a lower one there (an idle lane's sums are not used)
+          const int u0 = kprev - k0;
           const int32_t s = shift_sum(kprev);
 #pragma unroll
           for (int u = 0; u < kHeldShifts; ++u) {
@@ -1756,9 +1759,10 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
   P.batch = a.batch;
   // Lanes per NIC-lane set (a power of two) and shifts per lane: up to four
   // lanes, a quad, combine by two cheap steps, so the shifts of a set go to a
-  // quad where the wavefront has room (two, four or eight shifts per lane),
-  // to more lanes only beyond eight shifts each.  Sets that then do not fit
-  // a wavefront's 64 lanes are summed again in every iteration.
+  // quad where the wavefront has room, to more lanes only beyond eight shifts
+  // each.  Held shifts per lane are two, four or eight, as many as the kernel's
+  // loops over them run; the last lanes may hold none.  Sets that then do not
+  // fit a wavefront's 64 lanes are summed again in every iteration.
   {
     const int shifts = std::max(1, L.nn - 1), sets = std::max(1, L.max_sets);
     int lg = 0;
@@ -1767,7 +1771,7 @@ vp_status launch_plan(const PlanLaunch& a, void* stream) {
     P.LPS_log2 = lg;
     int spt = (shifts + (1 << lg) - 1) >> lg;
     P.held = (sets << lg) <= 64 && spt <= kHeldShifts;
-    P.SPT = spt;
+    P.SPT = !P.held ? spt : spt <= 2 ? 2 : spt <= 4 ? 4 : kHeldShifts;
   }
 
   int dev = 0;

@@ -223,3 +223,16 @@ def test_quantum_of_a_refused_demand(vp, nodes, unit, entries, k_target):
     assert vp.read_status(st) == vp.UNSUPPORTED and int(out["K"]) == 0
     den = topo.pcie_bytes_per_ns * k_target
     assert int(out["tau"]) == -(-int(max(D.sum(0).max(), D.sum(1).max())) // den)
+
+
+# Shifts that tie, at every number of them that the lanes of a set can share: demands of one unit, small caps
+@pytest.mark.parametrize("topo", [vpgen.Topology(n) for n in (10, 13, 17, 18, 20, 22, 25, 27, 32)] +
+                         [vpgen.Topology(66, 1, 2, 2, 2), vpgen.Topology(43, 1, 3, 3), vpgen.Topology(41, 1, 1, 2)],
+                         ids=lambda t: "x".join(map(str, t.as_tuple()[:5])))
+@pytest.mark.parametrize("per_row,seed", [(1, 0), (2, 0), (2, 1), (6, 0)])
+def test_ties_between_shifts(vp, topo, per_row, seed):
+    N = topo.n_ranks
+    rng = np.random.default_rng(N + per_row + 1000 * seed)
+    D = ((rng.random((N, N)) < per_row / N) * UNIT).astype(np.int64)
+    np.fill_diagonal(D, 0)
+    check(vp, topo, D, k_target=4 * N, k_max=120)
