@@ -128,8 +128,8 @@ def test_sys_topology_256_ranks_plan_parity(vp):
 
 def test_plan_state_beyond_lds_is_refused_on_host(vp):
     """Two nodes of two sockets x two switches x three GPUs with cross-socket
-    peer to peer give 2,185 shapes and 2,744 families, whose planner tables do
-    not fit in one workgroup's LDS: vp_plan refuses the catalog on the host
+    peer to peer give 2,185 shapes and 2,744 families, whose size measure
+    exceeds one workgroup's LDS: vp_plan refuses the catalog on the host
     with VP_ERR_UNSUPPORTED and enqueues nothing (the outputs keep their
     sentinel), and a plan on a catalog that fits still runs afterwards."""
     topo = vpgen.Topology(2, 2, 2, 3, 1, 32, 12, vp.TOPO_SYS_P2P)
